@@ -27,6 +27,8 @@
 //    stages its rows in the other half of a double-buffered row area.  The
 //    last chunk's refill then requests the next unit's first chunk, so a unit
 //    boundary costs no round trip.
+// Launches with fewer groups than that keeps busy take attn_team_kernel, whose
+// workgroups share a unit between their wavefronts (see there).
 // The workgroups own contiguous ranges of a permuted unit order (groups of a
 // (layer, sequence, split) spread over the whole range), so that ragged
 // selections even out across workgroups.  Pipelined launches over batches
@@ -123,6 +125,7 @@ struct AttnArgs {
                           // (g perm) mod n_groups, perm coprime to n_groups
   int n_sets;             // 1: idx [B][k_max]; H_kv: idx [B][H_kv][k_max], one set per KV head
   float scale_log2;       // scale * log2(e)
+  int team_heads;         // team kernel: column groups of a workgroup's wavefronts
   int sorted;             // pipelined launches: groups by selection size (see attn_split_kernel)
 };
 
@@ -249,38 +252,22 @@ __device__ __forceinline__ void store_v_rows(const int* rc, const uint4 (&vr)[kV
   }
 }
 
-// One unit from a cold start (a wavefront with a single unit): count, then
-// indices staged in LDS, then the first chunk.
+// A wavefront's tokens of one (layer, sequence, KV head) group, whose row
+// values are staged in `rows`: n_tok tokens, and one chunk of padding after
+// the last whole or partial chunk.  Local chunk c / kChunk holds the tokens
+// (slots) slot0 + c cstride ..: consecutive chunks (cstride 1), or every
+// cstride-th chunk of the selection.  Leaves the running maximum and sum of
+// head r16 (the sum not yet added over the four lanes of a head) and the
+// accumulators O^T[16db + 4kg + i][head r16].
 template <int KV>
-__device__ __forceinline__ void process_item(const AttnArgs& a, const int item, const int lane,
-                                             uint16_t* V, int* rows) {
-  // A group of more than 16 query heads is covered by R column groups of
-  // 16 (gv = g R .. g R + R - 1), each a unit of its own that reads KV head
-  // g; the query heads of column group gv are gv G .. gv G + G - 1.
-  const int G = a.G;
-  const int gv = item % (a.H_kv * a.R);
-  const int g = gv / a.R;
-  const int rest = item / (a.H_kv * a.R);
-  const int split = rest % a.n_split;
-  const int lb = rest / a.n_split;  // layer * B + b
+__device__ __forceinline__ void attend(const AttnArgs& a, const int lb, const int gv,
+                                       const int slot0, const int cstride, const int n_tok,
+                                       const int* rows, const bf16x8 (&qf)[4], uint16_t* V,
+                                       const int lane, float& m_run, float& l_run,
+                                       floatx4 (&acc)[8]) {
   const int b = lb % a.B;
   const int layer = lb / a.B;
-  const int count = __builtin_amdgcn_readfirstlane(clampi(a.counts[b], 0, a.k_max));
-  const int j0 = split * a.split_tokens;
-  const int r16e = lane & 15;
-  if (j0 >= count) {  // uniform per wavefront
-    if (a.mode == kDirect && r16e < G) {  // no tokens: out = 0, lse = -inf
-      const size_t orow = (size_t)lb * a.H_q + (size_t)gv * G + r16e;
-      float* dst = a.out + orow * kD + 4 * (lane >> 4);
-#pragma unroll
-      for (int db = 0; db < 8; ++db)
-        *reinterpret_cast<float4*>(dst + 16 * db) = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (a.lse && (lane >> 4) == 0) a.lse[orow] = -INFINITY;
-    }
-    return;
-  }
-  const int n_tok = min(a.split_tokens, count - j0);  // tokens of this work item
-
+  const int g = gv / a.R;
   const int64_t rs = (int64_t)a.H_kv * kD;  // elements per token row
   // kb/vb: the rows a staged row value r >= 0 addresses (the cache, or the
   // slot buffers in compact mode); kbf/vbf: elastic mode's slot buffers, for
@@ -292,51 +279,8 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
   uint16_t* kbf = a.kbuf + boff;
   uint16_t* vbf = a.vbuf + boff;
   const bool writer = KV == kKvElastic && gv % a.R == 0;  // one column group writes the slots
-
   const int r16 = lane & 15;  // head of this lane (MFMA column); token of a K tile row
   const int kg = lane >> 4;   // MFMA k-group; also the token phase of V loads
-  // B operand of S^T = K Q^T: Q^T column r16 = query head gv*G + r16 (zero if >= G),
-  // dims 32s + 8kg .. +8.  Loaded together with the row indices.
-  bf16x8 qf[4];
-  {
-    const uint16_t* qp = a.q + ((size_t)lb * a.H_q + gv * G + (r16 < G ? r16 : 0)) * kD + 8 * kg;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      uint4 w = r16 < G ? ldg16(qp + 32 * s) : make_uint4(0, 0, 0, 0);
-      qf[s] = __builtin_bit_cast(bf16x8, w);
-    }
-  }
-
-  // Stage the rows of this item's tokens in LDS (masked tokens read row 0),
-  // so that no chunk waits on an index load from memory.
-  wave_sync_lds();  // the previous item's reads of rows/V are done
-  {
-    // All index loads are issued before any is used (one round trip), and
-    // one chunk of padding follows the end: the software pipeline always
-    // prefetches the next chunk, and padding rows all read row 0 (cache hits).
-    const int32_t* idx_b =
-        KV == kKvIndexed ? a.idx + ((size_t)b * a.n_sets + (a.n_sets > 1 ? g : 0)) * a.k_max + j0
-        : KV == kKvElastic ? a.src + (size_t)b * a.k_max + j0
-                           : nullptr;
-    const bool fz = KV == kKvElastic && (a.fused == nullptr || a.fused[b] != 0);
-    const int n_pad = (n_tok + kChunk - 1) / kChunk * kChunk + kChunk;
-    constexpr int kColdRowLoads = (kMaxSplit + kChunk + 63) / 64;
-    int rv[kColdRowLoads];
-#pragma unroll
-    for (int m = 0; m < kColdRowLoads; ++m) {
-      const int j = lane + 64 * m;
-      rv[m] = KV == kKvElastic ? -1 : 0;  // padding: the unit's first slot, or row 0
-      if (j < n_tok && (KV != kKvElastic || fz)) rv[m] = KV == kKvCompact ? j0 + j : idx_b[j];
-    }
-#pragma unroll
-    for (int m = 0; m < kColdRowLoads; ++m) {
-      const int j = lane + 64 * m;
-      if (j < n_pad)
-        rows[j] = elastic_row<KV>(rv[m], j < n_tok ? j0 + j : j0, a.L_cap);
-    }
-  }
-
-  wave_sync_lds();
 
   // K rows in the MFMA A-operand layout: tile t, token 16t + r16, dims
   // 32s + 8kg .. +8.  V rows: load r brings token 4r + kg, dims 8 r16 .. +8,
@@ -357,8 +301,8 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
       vr[r] = ldkv(row_ptr<KV>(vb, vbf, rc[4 * r + kg], rs) + 8 * r16);
   };
 
-  float m_run = -INFINITY, l_run = 0.f;  // head r16
-  floatx4 acc[8];                        // O^T[16db + 4kg + i][head r16]
+  m_run = -INFINITY;
+  l_run = 0.f;
 #pragma unroll
   for (int db = 0; db < 8; ++db) acc[db] = floatx4{0.f, 0.f, 0.f, 0.f};
 
@@ -374,10 +318,11 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
   load_k(0, kraw);
   __builtin_amdgcn_sched_barrier(0);
   for (int c = 0; c < n_tok; c += kChunk) {
+    const int64_t slot = slot0 + (int64_t)c * cstride;  // elastic: the chunk's first slot
 #pragma unroll
     for (int r = 0; r < kVRows; ++r)
       *reinterpret_cast<uint4*>(V + (4 * r + kg) * kVPitch + 8 * r16) = vraw[r];
-    if (writer) store_v_rows(rows + c, vraw, vbf + (int64_t)(j0 + c) * rs, rs, n_tok - c, kg, r16);
+    if (writer) store_v_rows(rows + c, vraw, vbf + slot * rs, rs, n_tok - c, kg, r16);
     load_v(c + kChunk, vraw);
     __builtin_amdgcn_sched_barrier(0);  // keep the refill here: issue order = retire order
 
@@ -391,7 +336,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
         sacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kraw[t][s]),
                                                           qf[s], sacc[t], 0, 0, 0);
     }
-    if (writer) store_k_rows(rows + c, kraw, kbf + (int64_t)(j0 + c) * rs, rs, n_tok - c, kg, r16);
+    if (writer) store_k_rows(rows + c, kraw, kbf + slot * rs, rs, n_tok - c, kg, r16);
     load_k(c + kChunk, kraw);
     __builtin_amdgcn_sched_barrier(0);
 
@@ -407,13 +352,15 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
       }
     mx = xgroup_max(mx);
     const float mn = fmaxf(m_run, mx);
-    const float alpha = exp2f(m_run - mn);
+    // logits of -inf alone so far: a finite reference keeps their weights 0
+    const float ref = mn == -INFINITY ? 0.f : mn;
+    const float alpha = exp2f(m_run - ref);
     float ls = 0.f;
 #pragma unroll
     for (int t = 0; t < kTiles; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        sv[t][i] = exp2f(sv[t][i] - mn);
+        sv[t][i] = exp2f(sv[t][i] - ref);
         ls += sv[t][i];
       }
     l_run = l_run * alpha + ls;
@@ -448,6 +395,90 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
     }
     wave_sync_lds();  // the V tile is rewritten by the next chunk
   }
+}
+
+// B operand of S^T = K Q^T: Q^T column r16 = query head gv*G + r16 (zero if
+// >= G), dims 32s + 8kg .. +8.
+__device__ __forceinline__ void load_q(const AttnArgs& a, int lb, int gv, int lane,
+                                       bf16x8 (&qf)[4]) {
+  const int r16 = lane & 15, kg = lane >> 4;
+  const uint16_t* qp =
+      a.q + ((size_t)lb * a.H_q + gv * a.G + (r16 < a.G ? r16 : 0)) * kD + 8 * kg;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    uint4 w = r16 < a.G ? ldg16(qp + 32 * s) : make_uint4(0, 0, 0, 0);
+    qf[s] = __builtin_bit_cast(bf16x8, w);
+  }
+}
+
+// One unit from a cold start (a wavefront with a single unit): count, then
+// indices staged in LDS, then the first chunk.
+template <int KV>
+__device__ __forceinline__ void process_item(const AttnArgs& a, const int item, const int lane,
+                                             uint16_t* V, int* rows) {
+  // A group of more than 16 query heads is covered by R column groups of
+  // 16 (gv = g R .. g R + R - 1), each a unit of its own that reads KV head
+  // g; the query heads of column group gv are gv G .. gv G + G - 1.
+  const int G = a.G;
+  const int gv = item % (a.H_kv * a.R);
+  const int g = gv / a.R;
+  const int rest = item / (a.H_kv * a.R);
+  const int split = rest % a.n_split;
+  const int lb = rest / a.n_split;  // layer * B + b
+  const int b = lb % a.B;
+  const int count = __builtin_amdgcn_readfirstlane(clampi(a.counts[b], 0, a.k_max));
+  const int j0 = split * a.split_tokens;
+  const int r16 = lane & 15;  // head of this lane
+  const int kg = lane >> 4;
+  if (j0 >= count) {  // uniform per wavefront
+    if (a.mode == kDirect && r16 < G) {  // no tokens: out = 0, lse = -inf
+      const size_t orow = (size_t)lb * a.H_q + (size_t)gv * G + r16;
+      float* dst = a.out + orow * kD + 4 * kg;
+#pragma unroll
+      for (int db = 0; db < 8; ++db)
+        *reinterpret_cast<float4*>(dst + 16 * db) = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (a.lse && kg == 0) a.lse[orow] = -INFINITY;
+    }
+    return;
+  }
+  const int n_tok = min(a.split_tokens, count - j0);  // tokens of this work item
+
+  bf16x8 qf[4];  // loaded together with the row indices
+  load_q(a, lb, gv, lane, qf);
+
+  // Stage the rows of this item's tokens in LDS (masked tokens read row 0),
+  // so that no chunk waits on an index load from memory.
+  wave_sync_lds();  // the previous item's reads of rows/V are done
+  {
+    // All index loads are issued before any is used (one round trip), and
+    // one chunk of padding follows the end: the software pipeline always
+    // prefetches the next chunk, and padding rows all read row 0 (cache hits).
+    const int32_t* idx_b =
+        KV == kKvIndexed ? a.idx + ((size_t)b * a.n_sets + (a.n_sets > 1 ? g : 0)) * a.k_max + j0
+        : KV == kKvElastic ? a.src + (size_t)b * a.k_max + j0
+                           : nullptr;
+    const bool fz = KV == kKvElastic && (a.fused == nullptr || a.fused[b] != 0);
+    const int n_pad = (n_tok + kChunk - 1) / kChunk * kChunk + kChunk;
+    constexpr int kColdRowLoads = (kMaxSplit + kChunk + 63) / 64;
+    int rv[kColdRowLoads];
+#pragma unroll
+    for (int m = 0; m < kColdRowLoads; ++m) {
+      const int j = lane + 64 * m;
+      rv[m] = KV == kKvElastic ? -1 : 0;  // padding: the unit's first slot, or row 0
+      if (j < n_tok && (KV != kKvElastic || fz)) rv[m] = KV == kKvCompact ? j0 + j : idx_b[j];
+    }
+#pragma unroll
+    for (int m = 0; m < kColdRowLoads; ++m) {
+      const int j = lane + 64 * m;
+      if (j < n_pad)
+        rows[j] = elastic_row<KV>(rv[m], j < n_tok ? j0 + j : j0, a.L_cap);
+    }
+  }
+  wave_sync_lds();
+
+  float m_run, l_run;  // head r16
+  floatx4 acc[8];      // O^T[16db + 4kg + i][head r16]
+  attend<KV>(a, lb, gv, j0, 1, n_tok, rows, qf, V, lane, m_run, l_run, acc);
 
   l_run = xgroup_sum(l_run);
   if (r16 < G) {
@@ -475,6 +506,136 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
   }
 }
 
+// Launches with too few groups to give every wavefront of the chip a unit of
+// its own (team_plan): a workgroup of W wavefronts works on team_heads (layer,
+// sequence, KV head) groups, or on one of n_split parts of them, P = W /
+// team_heads wavefronts to each, and merges a group's wavefronts in LDS.
+// Such a launch is bound by its chain of round trips and by the ~31 GB/s that
+// one CU streams, so what counts is that every CU takes part, that few
+// partial results are left, and that the chain is short: chunk c of the
+// selection belongs to wavefront c mod (P n_split) of the group, whatever the
+// selection's length, so that no index address depends on the count (the
+// count, the indices and the queries arrive in one round trip) and a short
+// selection divides as evenly as a long one.
+constexpr int kTeamRows = 512;  // tokens per wavefront at most
+
+template <int KV, int W>
+__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W > 4 ? 2 : 1)))
+void attn_team_kernel(AttnArgs a) {
+  __shared__ __align__(16) uint16_t vlds[W][kChunk * kVPitch];
+  __shared__ int rows_lds[W][kTeamRows + kChunk];
+  __shared__ float2 ml_lds[W][16];
+  // a wavefront's results, once it has no more use for its V tile: 16 heads
+  // of 128 floats, 132 apart
+  constexpr int kMPitch = kD + 4;
+  static_assert(16 * kMPitch * sizeof(float) <= kChunk * kVPitch * sizeof(uint16_t), "merge area");
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int G = a.G;
+  const int hb = a.H_kv * a.R / a.team_heads;  // workgroups over the heads
+  const int gv0 = blockIdx.x % hb * a.team_heads;
+  const int gv = gv0 + wave % a.team_heads;
+  const int g = gv / a.R;
+  const int rest = blockIdx.x / hb;
+  const int split = rest % a.n_split;
+  const int lb = rest / a.n_split;  // layer * B + b
+  const int b = lb % a.B;
+  const int r16 = lane & 15;
+  const int kg = lane >> 4;
+  const int P = W / a.team_heads;       // wavefronts per head
+  const int NW = P * a.n_split;         // wavefronts of the group
+  const int gw = split * P + wave / a.team_heads;  // this one
+  uint16_t* V = vlds[wave];
+  int* rows = rows_lds[wave];
+
+  // count, queries and this wavefront's indices: independent of each other.
+  // Lane l of load m holds the token of local row 64 m + l.
+  const int cnt_raw = a.counts[b];
+  const int fz_raw = KV == kKvElastic && a.fused ? a.fused[b] : 1;
+  bf16x8 qf[4];
+  load_q(a, lb, gv, lane, qf);
+  const int32_t* idx_b =
+      KV == kKvIndexed ? a.idx + ((size_t)b * a.n_sets + (a.n_sets > 1 ? g : 0)) * a.k_max
+      : KV == kKvElastic ? a.src + (size_t)b * a.k_max
+                         : nullptr;
+  auto token = [&](int j) { return kChunk * (gw + NW * (j / kChunk)) + j % kChunk; };
+  const int most = (a.k_max + kChunk * NW - 1) / (kChunk * NW) * kChunk;  // <= kTeamRows (host)
+  constexpr int kLoads = kTeamRows / 64;
+  int rv[kLoads];
+#pragma unroll
+  for (int m = 0; m < kLoads; ++m) {
+    // rows past the index row re-read its last entry (one cache line)
+    const int t = token(lane + 64 * m);
+    rv[m] = 0;
+    if (64 * m < most) rv[m] = KV == kKvCompact ? t : idx_b[min(t, a.k_max - 1)];
+  }
+  const int count = __builtin_amdgcn_readfirstlane(clampi(cnt_raw, 0, a.k_max));
+  const bool fz = __builtin_amdgcn_readfirstlane(fz_raw) != 0;
+  // this wavefront's tokens: whole chunks, the selection's last one perhaps partial
+  const int n_chunks = (count + kChunk - 1) / kChunk;
+  const int mine = n_chunks > gw ? (n_chunks - gw + NW - 1) / NW : 0;
+  const int n_tok = mine == 0 ? 0
+                    : kChunk * mine - ((n_chunks - 1) % NW == gw ? kChunk * n_chunks - count : 0);
+  const int pad = KV == kKvElastic ? -1 - kChunk * gw : 0;  // its first slot, or row 0
+#pragma unroll
+  for (int m = 0; m < kLoads; ++m) {
+    const int j = lane + 64 * m;
+    if (64 * m < most + kChunk)
+      rows[j] = j < n_tok ? elastic_row<KV>(fz ? rv[m] : -1, token(j), a.L_cap) : pad;
+  }
+  if (lane < kChunk) rows[kTeamRows + lane] = pad;
+  wave_sync_lds();
+
+  float m_run = -INFINITY, l_run = 0.f;
+  floatx4 acc[8];
+  if (n_tok > 0) {  // uniform per wavefront
+    attend<KV>(a, lb, gv, kChunk * gw, NW, n_tok, rows, qf, V, lane, m_run, l_run, acc);
+    l_run = xgroup_sum(l_run);
+    float* dst = reinterpret_cast<float*>(V) + r16 * kMPitch + 4 * kg;
+#pragma unroll
+    for (int db = 0; db < 8; ++db)
+      *reinterpret_cast<float4*>(dst + 16 * db) =
+          make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+  }
+  if (kg == 0) ml_lds[wave][r16] = make_float2(m_run, l_run);
+  __syncthreads();
+  if (a.mode == kGlobalPartials && split * P >= n_chunks) return;  // no tokens: no partial
+
+  // Merge: thread = (head, 4 dims); the wavefronts' results in order.
+  for (int e = threadIdx.x; e < a.team_heads * G * (kD / 4); e += W * 64) {
+    const int d4 = e % (kD / 4);
+    const int hh = e / (kD / 4);  // query head among the workgroup's
+    const int hs = hh / G;        // its column group: wavefronts hs, hs + team_heads, ..
+    const int h = hh - hs * G;
+    float M = -INFINITY;
+    for (int w = hs; w < W; w += a.team_heads) M = fmaxf(M, ml_lds[w][h].x);
+    float L = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int w = hs; w < W; w += a.team_heads) {
+      const float2 ml = ml_lds[w][h];
+      if (ml.x == -INFINITY && ml.y == 0.f) continue;  // no tokens: nothing was written
+      const float f = ml.x == M ? 1.f : exp2f(ml.x - M);
+      const float4 x =
+          reinterpret_cast<const float4*>(reinterpret_cast<const float*>(vlds[w]) + h * kMPitch)[d4];
+      L += ml.y * f;
+      o.x += x.x * f;
+      o.y += x.y * f;
+      o.z += x.z * f;
+      o.w += x.w * f;
+    }
+    if (a.mode == kDirect) {
+      const size_t orow = (size_t)lb * a.H_q + (size_t)gv0 * G + hh;
+      const float inv = count > 0 ? 1.f / L : 0.f;
+      reinterpret_cast<float4*>(a.out + orow * kD)[d4] =
+          make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+      if (a.lse && d4 == 0) a.lse[orow] = count > 0 ? (M + log2f(L)) * kLn2 : -INFINITY;
+    } else {
+      const size_t prow = ((size_t)lb * a.n_split + split) * a.H_q + (size_t)gv0 * G + hh;
+      reinterpret_cast<float4*>(a.part_acc + prow * kD)[d4] = o;
+      if (d4 == 0) reinterpret_cast<float2*>(a.part_ml)[prow] = make_float2(M, L);
+    }
+  }
+}
 
 // Dynamic LDS requested on top of the static arrays so that one workgroup
 // takes more than half of a CU's 160 KiB: exactly one per CU.
@@ -846,41 +1007,50 @@ struct CombineArgs {
   int B, H_q, k_max, n_split, split_tokens;
 };
 
-// One workgroup per (layer*B + b, group of 8 heads); thread = (head, 4 dims).
-// The splits' (max, sum) pairs and accumulator slices are requested eight at
-// a time, all before any is used (one round trip for up to eight splits).
+// One workgroup per (layer*B + b, 8 / S heads); thread = (head, part, 4 dims).
+// A thread's splits (part, part + S, ..) have their (max, sum) pairs and
+// accumulator slices requested eight at a time, all before any is used: one
+// round trip for up to 8 S splits.  S > 1: the S results of a head are merged
+// in LDS.
+template <int S>
 __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
   constexpr int kBatch = 8;
+  __shared__ float2 ml_lds[S > 1 ? 8 : 1];
+  __shared__ float4 acc_lds[S > 1 ? 8 : 1][32];
   const int lb = blockIdx.x;
-  const int h = blockIdx.y * 8 + (threadIdx.x >> 5);
+  const int slot = threadIdx.x >> 5;
+  const int h = blockIdx.y * (8 / S) + slot / S;
+  const int part = slot % S;
   const int d4 = threadIdx.x & 31;
-  if (h >= a.H_q) return;
+  if (S == 1 && h >= a.H_q) return;
   const int b = lb % a.B;
   const int count = clampi(a.counts[b], 0, a.k_max);
-  const int ns = (count + a.split_tokens - 1) / a.split_tokens;
+  const int ns = min(a.n_split, (count + a.split_tokens - 1) / a.split_tokens);
   float4* o = reinterpret_cast<float4*>(a.out + ((size_t)lb * a.H_q + h) * kD) + d4;
-  if (ns == 0) {
-    *o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (a.lse && d4 == 0) a.lse[(size_t)lb * a.H_q + h] = -INFINITY;
+  if (ns == 0) {  // uniform per workgroup
+    if (h < a.H_q && part == 0) {
+      *o = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (a.lse && d4 == 0) a.lse[(size_t)lb * a.H_q + h] = -INFINITY;
+    }
     return;
   }
-  const size_t base = (size_t)lb * a.n_split * a.H_q + h;  // row of split 0
+  const size_t base = (size_t)lb * a.n_split * a.H_q + min(h, a.H_q - 1);  // row of split 0
   const float2* ml2 = reinterpret_cast<const float2*>(a.part_ml);
   float M = -INFINITY, L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s0 = 0; s0 < ns; s0 += kBatch) {
+  for (int s0 = part; s0 < ns; s0 += kBatch * S) {
     float2 ml[kBatch];
     float4 pa[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {  // clamped: every load is issued
-      const size_t row = base + (size_t)min(s0 + u, ns - 1) * a.H_q;
+      const size_t row = base + (size_t)min(s0 + u * S, ns - 1) * a.H_q;
       ml[u] = ml2[row];
       pa[u] = reinterpret_cast<const float4*>(a.part_acc + row * kD)[d4];
     }
     float Mb = M;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
-      if (s0 + u < ns) Mb = fmaxf(Mb, ml[u].x);
+      if (s0 + u * S < ns) Mb = fmaxf(Mb, ml[u].x);
     const float r = exp2f(M - Mb);  // earlier batches onto the new maximum (0 at the first)
     L *= r;
     acc.x *= r;
@@ -889,7 +1059,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
     acc.w *= r;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (s0 + u < ns) {
+      if (s0 + u * S < ns) {
         const float w = exp2f(ml[u].x - Mb);
         L += ml[u].y * w;
         acc.x += pa[u].x * w;
@@ -899,6 +1069,29 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
       }
     }
     M = Mb;
+  }
+  if (S > 1) {
+    if (d4 == 0) ml_lds[slot] = make_float2(M, L);
+    acc_lds[slot][d4] = acc;
+    __syncthreads();
+    if (part != 0 || h >= a.H_q) return;
+    const int parts = min(S, ns);  // parts with a split
+    for (int p = 1; p < parts; ++p) M = fmaxf(M, ml_lds[slot + p].x);
+    const float r = exp2f(ml_lds[slot].x - M);
+    L *= r;
+    acc.x *= r;
+    acc.y *= r;
+    acc.z *= r;
+    acc.w *= r;
+    for (int p = 1; p < parts; ++p) {
+      const float w = exp2f(ml_lds[slot + p].x - M);
+      const float4 x = acc_lds[slot + p][d4];
+      L += ml_lds[slot + p].y * w;
+      acc.x += x.x * w;
+      acc.y += x.y * w;
+      acc.z += x.z * w;
+      acc.w += x.w * w;
+    }
   }
   const float inv = 1.f / L;
   *o = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
@@ -910,6 +1103,8 @@ constexpr int64_t kWaveSlots = (int64_t)kWaves * 256;
 
 struct AttnPlan {
   int mode, n_split, split;
+  int team;  // wavefronts of a workgroup that share a unit (attn_team_kernel), or 0
+  int team_heads;  // column groups those wavefronts cover: team / team_heads of them each
 };
 
 // Work units are (layer, sequence, KV head, split of the selection).  With at
@@ -917,35 +1112,79 @@ struct AttnPlan {
 // split and each unit writes its output (kDirect).  With fewer groups the
 // selections are split until there is about one unit per slot, but not below
 // kMinSplitTokens (each unit pays a start-up latency and a partial-result
-// store; kMinSplitSmall for launches too small to fill the CUs) nor above
-// kMaxSplit (the index staging area) (kGlobalPartials).
+// store) nor above kMaxSplit (the index staging area) (kGlobalPartials).
 // Units are numbered KV head fastest, so that the wavefronts of a workgroup
 // read the same selected tokens' rows for neighbouring heads at the same time:
 // those pieces share DRAM pages.  A split is a whole number of chunks.
 // Column groups of at most 16 query heads per KV head.
 int attn_col_groups(const Dims& d) { return d.G > 16 ? d.G / 16 : 1; }
 
-// A launch whose units of kMinSplitTokens would not reach one per four CUs
-// (a single short layer) is latency-bound: its units may go down to
-// kMinSplitSmall tokens, so that more CUs take part.  Launches above that
-// keep the larger units, whose start-up cost is then the larger one.
-constexpr int kMinSplitSmall = 64;
-constexpr int64_t kSmallLaunchUnits = 64;
+// Launches of at most 512 groups, which leave the chip short of units: a
+// workgroup of several wavefronts per unit (attn_team_kernel).  Either a group
+// is one workgroup's, which writes the output (no combine: ~3.5 us), or the
+// selections are split over as many four-wavefront workgroups as CUs.  The
+// choice follows a cost fitted to launches of 8 to 256 workgroups: a CU
+// streams its tokens at ~0.017 us each when few CUs stream, ~0.025 us when all
+// do.  Two heads per workgroup read neighbouring pieces of the same rows
+// (2-4% faster on splits of at least 64 groups; 128 groups, k = 2048: 32.2 ->
+// 30.0 us); fewer, larger partials are better below that.  us per launch, one
+// wavefront per unit -> this plan, one layer, 32 query heads, 8 KV heads:
+//   1 x k=128 8.8 -> 5.5, 1 x k=512 9.2 -> 8.3, 9 x k=321 15.1 -> 10.4,
+//   1 x k=4096 (64 query heads) 15.9 -> 11.4, 8 x k=2048 20.3 -> 19.6,
+//   60 x k=300 27.8 -> 18.4, 50 ragged, k=1200 58.0 -> 53.0;
+//   61 ragged, k=1500, 4 KV heads 47.4 -> 40.9; 24 layers x 2 ragged, k=1000 48.8 -> 42.6.
+// One wavefront per unit stays better where its units just fill the
+// wavefronts (256 groups, k = 4096, 1024 units: 96.3 against 102.5 us; k =
+// 2048: 55.0 against 56.4; 160 groups, k = 1536, 960 units, in a step: 26.1
+// against 26.6), with more than 512 groups, and for short selections of 256
+// groups or more (four chunks per wavefront).
+constexpr int kCUs = 256;  // fixed: the workspace size must not depend on the device
+// unit_tokens: tokens per unit of one wavefront each (attn_plan).
+bool team_plan(const Dims& d, int64_t groups, int64_t unit_tokens, AttnPlan* p) {
+  const int gu = d.H_kv * attn_col_groups(d);
+  const int64_t units = groups * ((d.k_max + unit_tokens - 1) / unit_tokens);
+  if (units <= kWaveSlots && units >= kWaveSlots / 16 * 15) return false;
+  if (groups >= kCUs && d.k_max <= 4 * kChunk) return false;
+  auto cost = [](int64_t wgs, int64_t tokens) { return tokens * (0.017 + 3e-5 * wgs); };
+  double best = 1e30;
+  // direct: one workgroup per group, or per two where they fill the CUs
+  const int dh = groups <= kCUs ? 1 : 2;  // heads per workgroup
+  const int64_t dw = groups / dh;
+  const int W = (int64_t)d.k_max * dh >= 512 ? 8 : 4;
+  if (gu % dh == 0 && dw <= kCUs && (dh == 1 || dw >= 3 * kCUs / 4) &&
+      W / dh * kTeamRows >= d.k_max) {
+    best = cost(dw, (int64_t)d.k_max * dh);
+    *p = {kDirect, 1, 0, W, dh};
+  }
+  // split: parts of at least a chunk per wavefront
+  const int sh = gu % 2 == 0 && groups >= 64 ? 2 : 1;
+  const int P = 4 / sh;
+  const int64_t chunks = (d.k_max + kChunk - 1) / kChunk;
+  int64_t ns = kCUs * sh / groups;
+  if (ns > (chunks + P - 1) / P) ns = (chunks + P - 1) / P;
+  if (ns >= 2 && ns * P * kTeamRows >= d.k_max) {
+    const int64_t tok = ((chunks + ns * P - 1) / (ns * P)) * P * kChunk;
+    const double c = 3.5 + cost(groups / sh * ns, tok * sh);
+    if (c < best) {
+      best = c;
+      *p = {kGlobalPartials, (int)ns, kChunk * P, 4, sh};
+    }
+  }
+  return best < 1e30;
+}
 
 AttnPlan attn_plan(const Dims& d) {
   const int64_t base = (int64_t)d.n_layers * d.B * d.H_kv * attn_col_groups(d);
   auto round_chunk = [](int64_t t) { return (t + kChunk - 1) / kChunk * kChunk; };
-  const int64_t min_split =
-      base * ((d.k_max + kMinSplitTokens - 1) / kMinSplitTokens) < kSmallLaunchUnits
-          ? kMinSplitSmall
-          : kMinSplitTokens;
   int64_t n_split = (kWaveSlots * kSlotUnits + base - 1) / base;
   int64_t split = round_chunk((d.k_max + n_split - 1) / n_split);
-  if (split < min_split) split = min_split;
+  if (split < kMinSplitTokens) split = kMinSplitTokens;
   if (split > kMaxSplit) split = kMaxSplit;
+  AttnPlan team;
+  if (team_plan(d, base, split, &team)) return team;
   n_split = (d.k_max + split - 1) / split;
-  if (n_split == 1) return {kDirect, 1, (int)round_chunk(d.k_max)};
-  return {kGlobalPartials, (int)n_split, (int)split};
+  if (n_split == 1) return {kDirect, 1, (int)round_chunk(d.k_max), 0, 1};
+  return {kGlobalPartials, (int)n_split, (int)split, 0, 1};
 }
 
 }  // namespace
@@ -962,8 +1201,6 @@ int device_cu_count() {
   return n;
 }
 
-int attn_split_tokens(const Dims& d) { return attn_plan(d).split; }
-
 size_t attn_ws_bytes(const Dims& d) {
   const AttnPlan pl = attn_plan(d);
   if (pl.mode != kGlobalPartials) return 0;
@@ -979,6 +1216,32 @@ void launch_split(dim3 grid, bool pipe, const AttnArgs& a, hipStream_t s) {
     attn_split_kernel<KV, true><<<grid, kWaves * 64, lds_reserve(true), s>>>(a);
   else
     attn_split_kernel<KV, false><<<grid, kWaves * 64, lds_reserve(false), s>>>(a);
+}
+
+template <int W>
+void launch_team_w(int kv, dim3 grid, const AttnArgs& a, hipStream_t s) {
+  if (kv == kKvIndexed) attn_team_kernel<kKvIndexed, W><<<grid, W * 64, 0, s>>>(a);
+  else if (kv == kKvCompact) attn_team_kernel<kKvCompact, W><<<grid, W * 64, 0, s>>>(a);
+  else attn_team_kernel<kKvElastic, W><<<grid, W * 64, 0, s>>>(a);
+}
+void launch_team(int kv, int W, dim3 grid, const AttnArgs& a, hipStream_t s) {
+  if (W == 4) launch_team_w<4>(kv, grid, a, s);
+  else launch_team_w<8>(kv, grid, a, s);
+}
+
+// Merges the partial results of split selections (a direct launch has none).
+hipError_t launch_combine(const Dims& d, const AttnPlan& pl, const float* part_acc,
+                          const float* part_ml, const int32_t* counts, float* out, float* lse,
+                          hipStream_t s) {
+  if (pl.mode != kGlobalPartials) return hipGetLastError();
+  CombineArgs c{part_acc, part_ml, counts, out, lse, d.B, d.H_q, d.k_max, pl.n_split, pl.split};
+  const unsigned lb = (unsigned)(d.n_layers * d.B);
+  auto heads = [&](int per) { return dim3(lb, (unsigned)((d.H_q + per - 1) / per)); };
+  if (pl.n_split <= 8) attn_combine_kernel<1><<<heads(8), 256, 0, s>>>(c);
+  else if (pl.n_split <= 16) attn_combine_kernel<2><<<heads(4), 256, 0, s>>>(c);
+  else if (pl.n_split <= 32) attn_combine_kernel<4><<<heads(2), 256, 0, s>>>(c);
+  else attn_combine_kernel<8><<<heads(1), 256, 0, s>>>(c);
+  return hipGetLastError();
 }
 
 hipError_t launch_attn_mode(const Dims& d, int kv, const uint16_t* q, const uint16_t* k,
@@ -1012,10 +1275,14 @@ hipError_t launch_attn_mode(const Dims& d, int kv, const uint16_t* q, const uint
   AttnArgs a{q, k, v, idx, kbuf, vbuf, src, fused, counts, part_acc, part_ml, out, lse,
              d.kv_stride_layer, d.kv_stride_b, d.B, d.H_q, d.H_kv, d.G / R, d.k_max, d.L_cap,
              pl.n_split, pl.split, (int)n_items, R, pl.mode, n_order, perm, d.n_sets,
-             d.scale * kLog2e, 0};
+             d.scale * kLog2e, pl.team_heads, 0};
   // One workgroup per CU, fewer only when there are fewer units than CUs:
   // with few units they are spread over all CUs (each CU's share of the
   // bandwidth is limited) rather than packed four to a CU.
+  if (pl.team) {
+    launch_team(kv, pl.team, dim3((unsigned)(n_items / pl.team_heads)), a, s);
+    return launch_combine(d, pl, part_acc, part_ml, counts, out, lse, s);
+  }
   const int n_cu = device_cu_count();
   const dim3 grid((unsigned)(n_items < n_cu ? n_items : n_cu));
   // SPEC_ATTN_SCHEDULE=cold runs every unit from a cold start even where a
@@ -1036,11 +1303,7 @@ hipError_t launch_attn_mode(const Dims& d, int kv, const uint16_t* q, const uint
     launch_split<kKvCompact>(grid, pipe, a, s);
   else
     launch_split<kKvElastic>(grid, pipe, a, s);
-  if (pl.mode != kGlobalPartials) return hipGetLastError();
-  CombineArgs c{part_acc, part_ml, counts, out, lse, d.B, d.H_q, d.k_max, pl.n_split, pl.split};
-  const dim3 g2(d.n_layers * d.B, (d.H_q + 7) / 8);
-  attn_combine_kernel<<<g2, 256, 0, s>>>(c);
-  return hipGetLastError();
+  return launch_combine(d, pl, part_acc, part_ml, counts, out, lse, s);
 }
 
 }  // namespace

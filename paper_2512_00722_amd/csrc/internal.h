@@ -97,9 +97,8 @@ inline size_t topk_lists_bytes(const Dims& d) {
 }
 inline size_t topk_ws_bytes(const Dims& d) { return topk_hist_bytes(d) + topk_lists_bytes(d); }
 
-// Attention: tokens of the selection per work unit, and the workspace for
-// partial results (zero unless a selection is split across workgroups).
-int attn_split_tokens(const Dims& d);
+// Attention: the workspace for partial results (zero unless a selection is
+// split across workgroups).
 size_t attn_ws_bytes(const Dims& d);
 
 // Elastic loading: per sequence the list of (slot, token) copies, then per

@@ -263,6 +263,58 @@ def test_pipelined_units_equal_cold_units(dev, case, monkeypatch):
             assert torch.equal(l_l[0], runs["auto"][0][1][layer]), layer
 
 
+# Launches whose workgroups share a unit between their wavefronts: counts at
+# the chunk and wavefront edges.  (n_layers, B, L_cap, H_q, H_kv, counts, k_max)
+TEAM_CASES = [
+    # direct, four wavefronts per group; empty and one-token selections
+    (1, 9, 400, 8, 2, [0, 1, 31, 32, 33, 127, 128, 129, 200], 200),
+    # direct, eight wavefronts per group (200 groups)
+    (1, 100, 700, 8, 2, [(61 * b) % 521 for b in range(100)], 520),
+    # direct, two groups per workgroup (400 groups)
+    (2, 50, 500, 32, 4, [(37 * b) % 301 for b in range(50)], 300),
+    # split, one group per workgroup: 12, 32 and 48 parts (one chunk per wavefront)
+    (1, 1, 1600, 32, 8, [1500], 1500),
+    (1, 1, 5000, 64, 8, [4096], 4096),
+    (1, 2, 6200, 8, 1, [6113, 2049], 6144),
+    # split, two groups per workgroup (64 and 96 groups), an empty sequence
+    (2, 4, 2100, 32, 8, [2048, 0, 1025, 63], 2048),
+    (1, 12, 1300, 16, 8, [(103 * b) % 1201 for b in range(12)], 1200),
+    # column groups of more than 16 query heads
+    (1, 3, 900, 64, 2, [600, 31, 577], 600),
+]
+
+
+@pytest.mark.parametrize("case", TEAM_CASES, ids=[str(c[:5]) + f"k{c[6]}" for c in TEAM_CASES])
+def test_shared_units(dev, case):
+    """Indexed attention against the oracle, compact attention over the
+    gathered rows with the same bits, and a selection whose first chunks hold
+    only logits of -inf (their weights are 0)."""
+    announce(f"attn shared units {case[:5]}")
+    g = torch.Generator().manual_seed(23 + sum(case[:5]))
+    q, K, V, idx, counts = _attn_inputs(case, g)
+    qd, Kd, Vd, idxd, cd = q.to(dev), K.to(dev), V.to(dev), idx.to(dev), counts.to(dev)
+    out, lse = spec.sparse_decode_attn(qd, Kd, Vd, cd, idx=idxd)
+    _check_attn(out.cpu().numpy(), lse.cpu().numpy(), q, K, V, idx, counts, case)
+    ks, vs = spec.gather(Kd, Vd, idxd, cd)
+    o2, l2 = spec.sparse_decode_attn(qd, ks, vs, cd)
+    assert torch.equal(out, o2) and torch.equal(lse, l2)
+
+    b = int(counts.argmax())                      # the longest selection
+    c = int(counts[b])
+    drop = min(40, c - 1)                         # more than one chunk
+    q2 = q.clone()
+    q2[..., 0] = 1.0
+    K2 = K.clone()
+    K2[:, b, idx[b, :drop].long(), :, 0] = float("-inf")
+    out, lse = spec.sparse_decode_attn(q2.to(dev), K2.to(dev), Vd, cd, idx=idxd)
+    sel = idx[b, drop:c].numpy()
+    for layer in range(case[0]):
+        want, wl = oracle.sparse_gqa_attention(f64(q2)[layer, b], f64(K)[layer, b],
+                                               f64(V)[layer, b], sel)
+        assert np.abs(out[layer, b].cpu().numpy() - want).max() <= TOL_ATTN
+        assert np.abs(lse[layer, b].cpu().numpy() - wl).max() <= TOL_ATTN
+
+
 # Pipelined launches over ragged batches with at least two (layer, sequence,
 # split) groups per workgroup on a 256-CU device (and at most 256
 # sequences): the groups are dealt to the workgroups by selection size.
