@@ -2,7 +2,8 @@
 
 Every step runs in the HIP kernels of libspecctx.so (gfx950); this module
 only marshals torch tensors (device memory, the current HIP stream) into the
-C ABI declared in include/spec.h.  There is no fallback: if the library is
+C ABI declared in include/spec.h: calls that hand over every buffer in native
+code (binding/fast.cpp), the others through ctypes.  There is no fallback: if the library is
 missing, importing the ops raises.
 
     import paper_2512_00722_amd as spec
@@ -15,6 +16,7 @@ missing, importing the ops raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from typing import Optional
 
@@ -115,11 +117,16 @@ class MlaDims(ctypes.Structure):
 
 
 _lib = None
+_fast = None  # native marshalling (binding/fast.cpp), loaded with the library
+# its entry points, in the order its init() takes their addresses
+_FAST_API = ["spec_workspace_size", "spec_score", "spec_topk", "spec_sparse_decode_attn",
+             "spec_step", "spec_retrieval_qk", "spec_mla_workspace_size",
+             "spec_mla_sparse_decode_attn"]
 
 
 def load_library(path: Optional[str] = None):
     """Load libspecctx.so (raises if it has not been built)."""
-    global _lib
+    global _lib, _fast
     if _lib is not None and path is None:
         return _lib
     p = path or lib_path
@@ -162,7 +169,13 @@ def load_library(path: Optional[str] = None):
     lib.spec_step_noalloc_max_bytes.argtypes = []
     lib.spec_step_noalloc_max_bytes.restype = ctypes.c_size_t
     if path is None:
-        _lib = lib
+        try:
+            fast = importlib.import_module(__name__ + "._fast")
+        except ImportError as e:
+            raise ImportError("the native binding has not been built: build it with `python -m "
+                              "paper_2512_00722_amd.build` (or __graft_entry__.build())") from e
+        fast.init(*(ctypes.cast(getattr(lib, name), P).value for name in _FAST_API))
+        _lib, _fast = lib, fast
     return lib
 
 
@@ -179,6 +192,16 @@ def _p(t: Optional[torch.Tensor]):
 
 def _stream(t: torch.Tensor):
     return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+
+
+def _raw_stream(t: torch.Tensor) -> int:
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
+
+
+def _plain(t) -> bool:
+    """A device tensor proper: its call may take the native marshalling, which
+    falls back to the checks here (None) for anything unusual."""
+    return type(t) is torch.Tensor and t.is_cuda
 
 
 def _need(t: torch.Tensor, name: str, dtype, ndim: int):
@@ -242,6 +265,11 @@ def score(q_r: torch.Tensor, K_r: torch.Tensor, seq_lens: torch.Tensor,
     with n_sets > 1 sets (one per KV head), the maximum over each group of
     H_r / n_sets heads ([B, n_sets, L_max]); -inf beyond seq_lens."""
     lib = load_library()
+    if out is not None and ws is not None and _plain(K_r):
+        st = _fast.score(q_r, K_r, seq_lens, L_max, scale_r, out, ws, n_sets, _raw_stream(K_r))
+        if st is not None:
+            _check(st, "spec_score")
+            return out
     _need(q_r, "q_r", torch.bfloat16, 3)
     _need(K_r, "K_r", torch.bfloat16, 4)
     B, L_cap, H_r, d_r = K_r.shape
@@ -270,6 +298,11 @@ def topk(scores: torch.Tensor, seq_lens: torch.Tensor, ks: torch.Tensor, k_max: 
     indices of the same leading shape [.., k_max] int32 padded with -1, and
     counts [B] int32."""
     lib = load_library()
+    if idx is not None and counts is not None and ws is not None and _plain(scores):
+        st = _fast.topk(scores, seq_lens, ks, k_max, idx, counts, ws, _raw_stream(scores))
+        if st is not None:
+            _check(st, "spec_topk")
+            return idx, counts
     if scores.dim() == 3:
         _need(scores, "scores", torch.float32, 3)
         B, n_sets, L_max = scores.shape
@@ -359,6 +392,11 @@ def sparse_decode_attn(q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, counts
     K/V are [n_layers, B, k_max, H_kv, d] and rows [0, counts[b]) are used.
     Returns (out fp32 [n_layers, B, H_q, d], lse fp32 [n_layers, B, H_q] or None)."""
     lib = load_library()
+    if out is not None and ws is not None and (lse is not None or not with_lse) and _plain(q):
+        st = _fast.attn(q, K, V, counts, idx, scale, out, lse, ws, _raw_stream(q))
+        if st is not None:
+            _check(st, "spec_sparse_decode_attn")
+            return out, lse
     _need(q, "q", torch.bfloat16, 4)
     _check_cache(K, V)
     n_layers, B, L_cap, H_kv, d = K.shape
@@ -510,6 +548,15 @@ def step(q_r, K_r, seq_lens, ks, q, K, V, k_max: int, L_max: Optional[int] = Non
     head_level selects one token set per KV head (idx [B, H_kv, k_max],
     scores [B, H_kv, L_max]) instead of one per sequence."""
     lib = load_library()
+    if outputs is not None and ws is not None and _plain(q) and (
+            elastic is None or type(elastic) is ElasticState):
+        held = None if elastic is None else (elastic.slot_tok, elastic.kbuf, elastic.vbuf,
+                                             elastic.n_changed, elastic.slot_src)
+        st = _fast.step(q_r, K_r, seq_lens, ks, q, K, V, k_max, L_max, scale_r, scale, held,
+                        outputs, head_level, ws, _raw_stream(q))
+        if st is not None:
+            _check(st, "spec_step")
+            return outputs
     dims, o = _step_args(q_r, K_r, seq_lens, ks, q, K, V, k_max, L_max, scale_r, scale,
                          with_scores, with_lse, outputs, head_level)
     ws, nws = _workspace(dims, OP_STEP, q.device, ws)
@@ -685,6 +732,12 @@ def retrieval_qk(tokens: torch.Tensor, pos: torch.Tensor, emb: torch.Tensor, w_q
     (nothing for positions outside [0, L_cap)).  tokens, pos: int32 [B];
     emb [vocab, hidden]; w_q, w_k [H_r * d_r, hidden] (bf16)."""
     lib = load_library()
+    if q_r is not None and ws is not None and _plain(K_r):
+        st = _fast.retrieval_qk(tokens, pos, emb, w_q, w_k, K_r, rope_base, yarn_scale,
+                                yarn_orig_ctx, yarn_alpha, yarn_beta, q_r, ws, _raw_stream(K_r))
+        if st is not None:
+            _check(st, "spec_retrieval_qk")
+            return q_r
     _need(emb, "emb", torch.bfloat16, 2)
     _need(w_q, "w_q", torch.bfloat16, 2)
     _need(w_k, "w_k", torch.bfloat16, 2)
@@ -735,6 +788,11 @@ def mla_sparse_decode_attn(q: torch.Tensor, ckv: torch.Tensor, w_uk: torch.Tenso
     counts [B] int32.  Returns (out fp32 [n_layers, B, H, d_v], lse fp32
     [n_layers, B, H] or None)."""
     lib = load_library()
+    if out is not None and ws is not None and (lse is not None or not with_lse) and _plain(q):
+        st = _fast.mla(q, ckv, w_uk, w_uv, idx, counts, scale, out, lse, ws, _raw_stream(q))
+        if st is not None:
+            _check(st, "spec_mla_sparse_decode_attn")
+            return out, lse
     _need(q, "q", torch.bfloat16, 4)
     _need(ckv, "ckv", torch.bfloat16, 4)
     _need(w_uk, "w_uk", torch.bfloat16, 4)

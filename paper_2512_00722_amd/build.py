@@ -2,6 +2,8 @@
 
     python -m paper_2512_00722_amd.build
 
+and the Python binding's native marshalling (_fast.so, host code) with g++.
+
 Objects are compiled in parallel into _build/ next to this file and linked
 into paper_2512_00722_amd/libspecctx.so (in-tree, so it travels with the
 source tree).  Every call recompiles.
@@ -63,11 +65,39 @@ def _compile(src: str) -> str:
     return obj
 
 
+FAST_LIB = os.path.join(PKG, "_fast.so")
+
+
+def build_binding() -> str:
+    """The Python binding's native marshalling: a CPython extension over
+    torch's tensor headers.  It calls the C ABI through addresses the binding
+    hands it, so it links against torch only (already loaded when imported)."""
+    import sysconfig
+
+    import torch
+
+    t = os.path.dirname(os.path.abspath(torch.__file__))
+    tmp = FAST_LIB + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared",
+           "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(t, "include"), "-I" + sysconfig.get_paths()["include"],
+           os.path.join(PKG, "binding", "fast.cpp"), "-o", tmp,
+           "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"binding build failed:\n{' '.join(cmd)}\n{r.stderr}")
+    os.replace(tmp, FAST_LIB)
+    return FAST_LIB
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sources()
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
+        fast = ex.submit(build_binding)
         objs = list(ex.map(_compile, srcs))
+        fast.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -117,8 +147,9 @@ def build_sanitized(verbose: bool = False) -> str:
 
 def clean():
     shutil.rmtree(BUILD_DIR, ignore_errors=True)
-    if os.path.exists(LIB):
-        os.remove(LIB)
+    for lib in (LIB, FAST_LIB):
+        if os.path.exists(lib):
+            os.remove(lib)
 
 
 if __name__ == "__main__":
