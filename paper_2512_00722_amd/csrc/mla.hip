@@ -38,11 +38,16 @@
 //     numbered 8 apart, which puts them on the same XCD (workgroups are
 //     dealt to the 8 XCDs in turn) at the same time: the second reads the
 //     latent rows from that XCD's L2.
-//  3. mla_out_kernel: one workgroup per (layer, head) merges the splits of
-//     every sequence into the latent output o~ (log-sum-exp), splits it into
-//     bf16 high + low parts in LDS and applies W_UV[h] on the matrix cores
-//     (A = 16 rows of W_UV streamed from HBM, B = o~ of up to 16 sequences),
-//     writing out and lse.
+//     Launches of few heads, or of more than 8 sequences, take
+//     mla_absorb_split_kernel instead.
+//  3. mla_out_kernel: two workgroups per (layer, head), one for each half of
+//     its value dims, merge the splits of every sequence into the latent
+//     output o~ (log-sum-exp), split it into bf16 high + low parts in LDS and
+//     apply W_UV[h] on the matrix cores (A = 16 rows of W_UV streamed from HBM,
+//     B = o~ of up to 16 sequences), writing out and lse.  One workgroup per
+//     head with the splits merged one after the other took 13.3 us on one
+//     layer (8 sequences, 8 splits), against 10.0 with two and four splits
+//     requested together; 61 layers 239 -> 209.
 #include "device_common.h"
 #include "internal.h"
 
@@ -237,6 +242,115 @@ __global__ __launch_bounds__(64) void mla_absorb_kernel(MlaArgs a) {
       if (lane < kDR / 8) {  // the rotary part, unchanged
         const uint16_t* src = a.q + (((size_t)layer * a.B + b) * a.H + h) * (kDN + kDR) + kDN;
         *reinterpret_cast<uint4*>(dst + 2 * kDC + 8 * lane) = ldg16(src + 8 * lane);
+      }
+    }
+  }
+}
+
+// The same for launches of few (layer, head) pairs, where one wavefront a head
+// leaves the chip idle and streams its 128 KiB alone (16.9 us for 128 heads):
+// a workgroup of four wavefronts per half of a head's latent dims.  Wavefront
+// w holds rows 32 w .. 32 w + 31 of the half in registers (sixteen 16-byte
+// loads a lane, all in flight at once: lane l has dims 8 (l mod 32) ..  and the
+// row pairs 2i + l / 32), so that W_UK is read once for any number of
+// sequences; the partial sums of its row pairs are added over the lane halves,
+// then over the wavefronts in LDS.
+//
+// us per call, one wavefront a head -> this: 1 layer x 128 heads, 8 sequences
+// (the kernel alone) 16.9 -> 7.9; 32 sequences, all three kernels 107 -> 62; 8
+// layers x 128 heads, 8 sequences, 141 -> 140; 16 layers 250 -> 255: there the
+// chip is full either way and the LDS sums cost more than they save, unless
+// more than 8 sequences would read W_UK again.
+constexpr int kAbsDims = kDC / 2;  // latent dims of a workgroup
+constexpr int kAbsSplitHeads = 1024;  // (layer, head) pairs up to which it is taken
+
+template <int TB>
+__global__ __launch_bounds__(kMThreads) void mla_absorb_split_kernel(MlaArgs a) {
+  __shared__ __align__(16) uint32_t qs2[TB][kDN / 2];  // (q[2p], q[2p+1]) as bf16 pairs
+  __shared__ __align__(16) float red[kMWaves][TB][kAbsDims];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int half = blockIdx.x & 1;
+  const int lh = blockIdx.x >> 1;  // layer * H + head
+  const int layer = lh / a.H;
+  const int h = lh - layer * a.H;
+  const int dl = 8 * (lane & 31);  // this lane's dims in the half
+  const int pl = lane >> 5;        // its row pairs
+  const uint16_t* w =
+      a.w_uk + ((size_t)lh * kDN + 32 * wave + 2 * pl) * kDC + kAbsDims * half + dl;
+  uint4 wr[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i)  // row 32 wave + 4 (i / 2) + 2 pl + i mod 2
+    wr[i] = ldg16_stream(w + (size_t)(4 * (i >> 1) + (i & 1)) * kDC);
+  for (int b0 = 0; b0 < a.B; b0 += TB) {
+    __syncthreads();  // the previous pass is done with qs2 and red
+    for (int e = tid; e < TB * (kDN / 8); e += kMThreads) {
+      const int t = e / (kDN / 8), n8 = e - t * (kDN / 8);
+      const int b = min(b0 + t, a.B - 1);
+      *reinterpret_cast<uint4*>(&qs2[t][4 * n8]) =
+          ldg16(a.q + (((size_t)layer * a.B + b) * a.H + h) * (kDN + kDR) + 8 * n8);
+    }
+    __syncthreads();
+    float acc[TB][8];
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[t][j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t* x = reinterpret_cast<const uint32_t*>(&wr[2 * i]);      // row n
+      const uint32_t* y = reinterpret_cast<const uint32_t*>(&wr[2 * i + 1]);  // row n+1
+      uint32_t wp[8];  // (W[n][c], W[n+1][c]) for this lane's 8 latent dims
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        wp[2 * j] = __builtin_amdgcn_perm(y[j], x[j], 0x05040100u);
+        wp[2 * j + 1] = __builtin_amdgcn_perm(y[j], x[j], 0x07060302u);
+      }
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        const uint32_t qp = qs2[t][16 * wave + 2 * i + pl];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[t][c] = dot2_bf16(wp[c], qp, acc[t][c]);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const auto o = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[t][j]),
+                                                        __float_as_uint(acc[t][j]), false, false);
+        acc[t][j] = __uint_as_float(o[0]) + __uint_as_float(o[1]);
+      }
+      // each lane half stores one half of the lane's dims
+      *reinterpret_cast<float4*>(&red[wave][t][dl + 4 * pl]) =
+          pl ? make_float4(acc[t][4], acc[t][5], acc[t][6], acc[t][7])
+             : make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    }
+    __syncthreads();
+    for (int e = tid; e < TB * (kAbsDims / 8); e += kMThreads) {
+      const int t = e / (kAbsDims / 8), c8 = 8 * (e % (kAbsDims / 8));
+      const int b = b0 + t;
+      if (b >= a.B) break;  // later items are of later sequences
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = 0.f;
+#pragma unroll
+      for (int u = 0; u < kMWaves; ++u)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] += red[u][t][c8 + j];
+      uint16_t* dst = a.qt + (((size_t)layer * a.B + b) * a.H + h) * kQT + kAbsDims * half + c8;
+      uint4 hi, lo;
+      split8(v, hi, lo);
+      *reinterpret_cast<uint4*>(dst) = hi;
+      *reinterpret_cast<uint4*>(dst + kDC) = lo;
+    }
+    if (half == 0 && tid < TB * (kDR / 8)) {  // the rotary part, unchanged
+      const int t = tid / (kDR / 8), n8 = tid % (kDR / 8);
+      if (b0 + t < a.B) {
+        const size_t row = ((size_t)layer * a.B + b0 + t) * a.H + h;
+        *reinterpret_cast<uint4*>(a.qt + row * kQT + 2 * kDC + 8 * n8) =
+            ldg16(a.q + row * (kDN + kDR) + kDN + 8 * n8);
       }
     }
   }
@@ -539,10 +653,13 @@ void mla_attn_kernel(MlaArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kOPitch = kDC + 8;  // LDS pitch of the o~ tiles (elements)
 
+// TB: sequences per pass (the product's 16 columns, or half of them).
+// kSplits: selections are split (else the partials are the one split's).
+template <int TB, bool kSplits>
 __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
-  __shared__ __align__(16) uint16_t ohi[16 * kOPitch];
-  __shared__ __align__(16) uint16_t olo[16 * kOPitch];
-  __shared__ float wsp[16][17];  // per sequence: split weights, then the lse
+  __shared__ __align__(16) uint16_t ohi[TB * kOPitch];
+  __shared__ __align__(16) uint16_t olo[TB * kOPitch];
+  __shared__ float wsp[TB][17];  // per sequence: split weights, then the lse
   __shared__ float2 wml[kMMaxSplitCount][16];  // per split and sequence: (max, sum)
 
   const int tid = threadIdx.x;
@@ -550,36 +667,52 @@ __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
   const int wave = tid >> 6;
   const int r16 = lane & 15;
   const int kg = lane >> 4;
-  const int layer = blockIdx.x / a.H;
-  const int h = blockIdx.x - layer * a.H;
-  const uint16_t* w = a.w_uv + ((size_t)layer * a.H + h) * kDVo * kDC;
+  // The two workgroups of a head are 8 apart: on one XCD (workgroups are dealt
+  // to the 8 in turn), whose L2 serves the partials to the second.  (H is a
+  // multiple of 8.)
+  const int lh = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7);  // layer * H + head
+  const int v0 = 64 * ((blockIdx.x >> 3) & 1) + 16 * wave;  // this wavefront's value dims
+  const int layer = lh / a.H;
+  const int h = lh - layer * a.H;
+  const uint16_t* w = a.w_uv + (size_t)lh * kDVo * kDC;
 
-  // this wavefront's rows of W_UV[h] (v-tiles 2w, 2w+1), requested first so
-  // that they stream in while the latent outputs are merged
-  uint4 wr[2][kDC / 32];
+  // this wavefront's rows of W_UV[h], requested first so that they stream in
+  // while the latent outputs are merged.  Plain loads: an instruction reads
+  // half a cache line of each row, and the next one the other half (marked
+  // non-temporal, the halves were fetched twice: 61 layers 209 -> 234 us).
+  uint4 wr[kDC / 32];
+  {
+    const uint16_t* wp = w + (size_t)(v0 + r16) * kDC + 8 * kg;
 #pragma unroll
-  for (int vt = 0; vt < 2; ++vt) {
-    const uint16_t* wp = w + (size_t)(32 * wave + 16 * vt + r16) * kDC + 8 * kg;
-#pragma unroll
-    for (int s = 0; s < kDC / 32; ++s) wr[vt][s] = ldg16_stream(wp + 32 * s);
+    for (int s = 0; s < kDC / 32; ++s) wr[s] = ldg16(wp + 32 * s);
   }
-  constexpr int kItems = 16 * (kDC / 8) / kMThreads;  // (sequence, 8 dims) items per thread
-  for (int b0 = 0; b0 < a.B; b0 += 16) {
-    // Everything the merge reads is requested before the first wait: the
-    // first split's partials of this thread's items and one (sequence, split)
+  constexpr int kItems = TB * (kDC / 8) / kMThreads;  // (sequence, 8 dims) items per thread
+  constexpr int kBatch = kSplits ? 8 / kItems : 1;    // splits requested together
+  for (int b0 = 0; b0 < a.B; b0 += TB) {
+    // Everything the merge reads first is requested before the first wait: the
+    // first splits' partials of this thread's items and one (sequence, split)
     // pair of (max, sum) per thread.  (Loads retire in order, so a chain of
-    // dependent loads here would queue each link behind the W_UV rows.)
-    float4 x0[kItems][2];
+    // dependent loads here would queue each link behind the W_UV rows.)  The
+    // other splits follow a batch at a time.
+    float4 x[kItems][kBatch][2];
+    auto request = [&](int s0) {
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-      const int e = tid + i * kMThreads;
-      const int t = e / (kDC / 8), c8 = e - t * (kDC / 8);
-      const int b = min(b0 + t, a.B - 1);
-      const float* src =
-          a.part_acc + (((size_t)layer * a.B + b) * a.n_split * a.H + h) * kDC + 8 * c8;
-      x0[i][0] = *reinterpret_cast<const float4*>(src);
-      x0[i][1] = *reinterpret_cast<const float4*>(src + 4);
-    }
+      for (int i = 0; i < kItems; ++i) {
+        const int e = tid + i * kMThreads;
+        const int t = e / (kDC / 8), c8 = e - t * (kDC / 8);
+        const int b = min(b0 + t, a.B - 1);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const int sp = min(s0 + u, a.n_split - 1);  // clamped: every load is issued
+          const float* src =
+              a.part_acc +
+              ((((size_t)layer * a.B + b) * a.n_split + sp) * a.H + h) * kDC + 8 * c8;
+          x[i][u][0] = *reinterpret_cast<const float4*>(src);
+          x[i][u][1] = *reinterpret_cast<const float4*>(src + 4);
+        }
+      }
+    };
+    request(0);
     static_assert(kMMaxSplitCount * 16 == kMThreads, "one (split, sequence) pair per thread");
     const int ms_s = tid >> 4;
     const int ms_b = min(b0 + (tid & 15), a.B - 1);
@@ -591,7 +724,7 @@ __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
     wml[ms_s][tid & 15] = ml;
     __syncthreads();
     // split weights w_s = 2^(m_s - M) / sum_s' 2^(m_s' - M) l_s' per sequence
-    if (tid < 16 && b0 + tid < a.B) {
+    if (tid < TB && b0 + tid < a.B) {
       float M = -INFINITY;
       for (int s = 0; s < a.n_split; ++s) M = fmaxf(M, wml[s][tid].x);
       float L = 0.f;
@@ -605,61 +738,58 @@ __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
       wsp[tid][16] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
     }
     __syncthreads();
-    // o~ of sequences b0 .. b0+15 as bf16 high + low parts (zero past B)
+    // o~ of sequences b0 .. b0+TB-1 as bf16 high + low parts (zero past B)
+    float v[kItems][8];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[i][j] = 0.f;
+    for (int s0 = 0; s0 < a.n_split; s0 += kBatch) {
+      if (s0 > 0) request(s0);
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        const int t = (tid + i * kMThreads) / (kDC / 8);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          if (s0 + u < a.n_split && b0 + t < a.B) {
+            const float ws = wsp[t][s0 + u];
+            const float4 y0 = x[i][u][0], y1 = x[i][u][1];
+            v[i][0] += ws * y0.x; v[i][1] += ws * y0.y; v[i][2] += ws * y0.z; v[i][3] += ws * y0.w;
+            v[i][4] += ws * y1.x; v[i][5] += ws * y1.y; v[i][6] += ws * y1.z; v[i][7] += ws * y1.w;
+          }
+        }
+      }
+    }
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
       const int e = tid + i * kMThreads;
       const int t = e / (kDC / 8), c8 = e - t * (kDC / 8);
-      const int b = b0 + t;
-      float v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = 0.f;
-      if (b < a.B) {
-        const size_t base = ((size_t)layer * a.B + b) * a.n_split;
-        for (int s = 0; s < a.n_split; ++s) {
-          const float ws = wsp[t][s];
-          float4 y0 = x0[i][0], y1 = x0[i][1];
-          if (s > 0) {
-            const float* src = a.part_acc + ((base + s) * a.H + h) * kDC + 8 * c8;
-            y0 = *reinterpret_cast<const float4*>(src);
-            y1 = *reinterpret_cast<const float4*>(src + 4);
-          }
-          v[0] += ws * y0.x; v[1] += ws * y0.y; v[2] += ws * y0.z; v[3] += ws * y0.w;
-          v[4] += ws * y1.x; v[5] += ws * y1.y; v[6] += ws * y1.z; v[7] += ws * y1.w;
-        }
-      }
       uint4 hi, lo;
-      split8(v, hi, lo);
+      split8(v[i], hi, lo);
       *reinterpret_cast<uint4*>(ohi + t * kOPitch + 8 * c8) = hi;
       *reinterpret_cast<uint4*>(olo + t * kOPitch + 8 * c8) = lo;
     }
     __syncthreads();
 
-    // out^T[v][b] = W_UV[h][v][:] . o~[b][:]: wavefront w owns v-tiles 2w, 2w+1.
-    floatx4 acc[2];
-#pragma unroll
-    for (int vt = 0; vt < 2; ++vt) acc[vt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // out^T[v][b] = W_UV[h][v][:] . o~[b][:]; columns past TB repeat earlier
+    // ones and are not stored.
+    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int col = r16 & (TB - 1);
 #pragma unroll
     for (int s = 0; s < kDC / 32; ++s) {
-      const uint4 bh = *reinterpret_cast<const uint4*>(ohi + r16 * kOPitch + 32 * s + 8 * kg);
-      const uint4 bl = *reinterpret_cast<const uint4*>(olo + r16 * kOPitch + 32 * s + 8 * kg);
-#pragma unroll
-      for (int vt = 0; vt < 2; ++vt) {
-        acc[vt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            __builtin_bit_cast(bf16x8, wr[vt][s]), __builtin_bit_cast(bf16x8, bh), acc[vt], 0, 0, 0);
-        acc[vt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            __builtin_bit_cast(bf16x8, wr[vt][s]), __builtin_bit_cast(bf16x8, bl), acc[vt], 0, 0, 0);
-      }
+      const uint4 bh = *reinterpret_cast<const uint4*>(ohi + col * kOPitch + 32 * s + 8 * kg);
+      const uint4 bl = *reinterpret_cast<const uint4*>(olo + col * kOPitch + 32 * s + 8 * kg);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          __builtin_bit_cast(bf16x8, wr[s]), __builtin_bit_cast(bf16x8, bh), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          __builtin_bit_cast(bf16x8, wr[s]), __builtin_bit_cast(bf16x8, bl), acc, 0, 0, 0);
     }
-    // lane (b = r16, kg) holds out[b][v = 32w + 16vt + 4kg + i]
+    // lane (b = r16, kg) holds out[b][v = v0 + 4kg + i]
     const int b = b0 + r16;
-    if (b < a.B) {
-      float* dst = a.out + (((size_t)layer * a.B + b) * a.H + h) * kDVo + 32 * wave + 4 * kg;
-#pragma unroll
-      for (int vt = 0; vt < 2; ++vt)
-        *reinterpret_cast<float4*>(dst + 16 * vt) =
-            make_float4(acc[vt][0], acc[vt][1], acc[vt][2], acc[vt][3]);
-      if (a.lse && wave == 0 && kg == 0)
+    if (r16 < TB && b < a.B) {
+      float* dst = a.out + (((size_t)layer * a.B + b) * a.H + h) * kDVo + v0 + 4 * kg;
+      *reinterpret_cast<float4*>(dst) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      if (a.lse && v0 == 0 && kg == 0)
         a.lse[((size_t)layer * a.B + b) * a.H + h] = wsp[r16][16];
     }
   }
@@ -743,19 +873,30 @@ hipError_t launch_mla(const MlaDims& d, const uint16_t* q, const uint16_t* ckv,
   const int grid_lh = d.n_layers * d.H;
   // a multiple of 16 keeps the two head groups of a unit on one XCD
   const int grid = p.n_items < n_cu ? p.n_items : (n_cu / 16 > 0 ? n_cu / 16 * 16 : n_cu);
-  const dim3 abs_block(64);
-  if (d.B == 1)
-    hipLaunchKernelGGL((mla_absorb_kernel<1>), dim3(grid_lh), abs_block, 0, s, a);
-  else if (d.B <= 4)
-    hipLaunchKernelGGL((mla_absorb_kernel<4>), dim3(grid_lh), abs_block, 0, s, a);
-  else
-    hipLaunchKernelGGL((mla_absorb_kernel<8>), dim3(grid_lh), abs_block, 0, s, a);
+  if (d.B > 8 || grid_lh <= kAbsSplitHeads) {
+    const dim3 g(2 * grid_lh), t(kMThreads);
+    if (d.B == 1) hipLaunchKernelGGL((mla_absorb_split_kernel<1>), g, t, 0, s, a);
+    else if (d.B <= 4) hipLaunchKernelGGL((mla_absorb_split_kernel<4>), g, t, 0, s, a);
+    else hipLaunchKernelGGL((mla_absorb_split_kernel<8>), g, t, 0, s, a);
+  } else {
+    const dim3 g(grid_lh), t(64);
+    if (d.B == 1) hipLaunchKernelGGL((mla_absorb_kernel<1>), g, t, 0, s, a);
+    else if (d.B <= 4) hipLaunchKernelGGL((mla_absorb_kernel<4>), g, t, 0, s, a);
+    else hipLaunchKernelGGL((mla_absorb_kernel<8>), g, t, 0, s, a);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((mla_attn_kernel<1>), dim3(grid), dim3(kMThreads), 0, s, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mla_out_kernel, dim3(grid_lh), dim3(kMThreads), 0, s, a);
+  const dim3 go(2 * grid_lh), to(kMThreads);
+  if (d.B <= 8) {
+    if (p.n_split > 1) hipLaunchKernelGGL((mla_out_kernel<8, true>), go, to, 0, s, a);
+    else hipLaunchKernelGGL((mla_out_kernel<8, false>), go, to, 0, s, a);
+  } else {
+    if (p.n_split > 1) hipLaunchKernelGGL((mla_out_kernel<16, true>), go, to, 0, s, a);
+    else hipLaunchKernelGGL((mla_out_kernel<16, false>), go, to, 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -89,6 +89,44 @@ def test_mla_cases(dev, case):
     print(f"max |out - oracle| = {worst:.2e}")
 
 
+# (B, L, k_max, n_layers, H, counts): both forms of the absorb kernel (one
+# wavefront a head above 1024 heads and up to 8 sequences; half heads
+# otherwise, in passes of 1, 4 or 8 sequences) and both of the output kernel
+# (8 and 16 sequences a pass), with a remainder in each, and split counts that
+# are no multiple of the splits it requests together
+FORM_CASES = [
+    (1, 80, 30, 17, 64, [30]),
+    (3, 80, 30, 17, 64, [30, 0, 7]),
+    (7, 80, 30, 17, 64, [30 - 4 * i for i in range(7)]),
+    (3, 1500, 1400, 1, 64, [1400, 600, 1]),
+    (8, 80, 30, 1, 64, [30 - i for i in range(8)]),
+    (9, 800, 700, 1, 64, [700 - 80 * i for i in range(9)]),
+    (17, 400, 300, 2, 64, [300 - 17 * i for i in range(17)]),
+]
+
+
+@pytest.mark.parametrize("case", FORM_CASES, ids=[f"B{c[0]}_k{c[2]}_l{c[3]}" for c in FORM_CASES])
+def test_mla_kernel_forms(dev, case):
+    B, L, k_max, n_layers, H, counts = case
+    announce(f"mla forms {case[:5]}")
+    w = small_workload(B=B, L=L, k=k_max, n_layers=n_layers, H_q=H, H_kv=1, mla=True)
+    x = generate_mla(w, seed=13, device=dev)
+    idx = _random_idx(np.random.default_rng(17), B, k_max, L, counts)
+    out, lse = spec.mla_sparse_decode_attn(
+        x["q_mla"], x["ckv"], x["w_uk"], x["w_uv"], torch.as_tensor(idx, device=dev),
+        torch.as_tensor(np.array(counts, dtype=np.int32), device=dev))
+    out, lse = out.cpu().numpy(), lse.cpu().numpy()
+    heads = np.array([0, 15, 16, 41, H - 1])
+    for layer in {0, n_layers - 1}:
+        for b in range(B):
+            if counts[b] == 0:
+                assert np.all(out[layer, b] == 0) and np.all(np.isneginf(lse[layer, b]))
+                continue
+            want, wl = _oracle(x, layer, b, idx[b, :counts[b]], heads=heads)
+            assert np.abs(out[layer, b][heads] - want).max() <= TOL_ATTN, (layer, b)
+            assert np.abs(lse[layer, b][heads] - wl).max() <= TOL_ATTN, (layer, b)
+
+
 def test_mla_strided_cache_and_repeat(dev):
     """A cache with padding between sequences and layers (strides from the
     tensor view) gives the same result as a packed one, bit for bit, and a
