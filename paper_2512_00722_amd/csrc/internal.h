@@ -22,22 +22,31 @@ struct Dims {
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// Retrieval scoring: tokens per workgroup of the logits kernel, 256, halved
-// (down to 64) while the grid would have fewer workgroups than the chip has
-// CUs: a short single sequence is latency-bound, and more, smaller blocks
-// keep more bytes in flight.
+// Retrieval scoring: tokens per workgroup of the logits kernel.  A CU streams
+// ~31 GB/s however many workgroups it holds, so the busiest CU sets the time:
+// the sequences are cut into as many blocks as a whole number of workgroups
+// per CU (at least two, for bytes in flight), of 64 to 256 tokens.  spec_score
+// in us, blocks of 256 halved only below one per CU -> this (with whole 16-byte
+// pieces per logits row, see score_row_stride): 16 x 4096 25.4 -> 22.8, 1 x
+// 65536 26.0 -> 24.0, 30 ragged x 3000 27.9 -> 23.9, 5 ragged x 20011 (16 heads)
+// 44.3 -> 39.0, 2 x 50000 (16 heads) 53.0 -> 49.6; rows that fill the CUs
+// evenly with 256 keep them (8 x 32768 55.5 -> 55.2).
 constexpr int kScoreTokensPerBlock = 256;
 constexpr int kScoreTokensPerBlockMin = 64;
-constexpr int64_t kScoreMinBlocks = 256;
+constexpr int64_t kScoreCUs = 256;  // fixed: the workspace size must not depend on the device
 // Softmax/head-sum kernel: tokens per workgroup.
 constexpr int kSoftTokensPerBlock = 1024;
 
 inline int score_tokens_per_block(const Dims& d) {
-  int tpb = kScoreTokensPerBlock;
-  while (tpb > kScoreTokensPerBlockMin &&
-         (int64_t)d.B * ((d.L_max + tpb - 1) / tpb) < kScoreMinBlocks)
-    tpb /= 2;
-  return tpb;
+  const int64_t total = (int64_t)d.B * d.L_max;
+  const int64_t round = kScoreCUs * kScoreTokensPerBlock;
+  const int64_t per_cu = total > 2 * round ? (total + round - 1) / round : 2;
+  const int64_t per_seq = kScoreCUs * per_cu / d.B;  // blocks of a sequence
+  if (per_seq < 1) return kScoreTokensPerBlock;
+  const int64_t t = ((d.L_max + per_seq - 1) / per_seq + 15) / 16 * 16;
+  return (int)(t < kScoreTokensPerBlockMin ? kScoreTokensPerBlockMin
+               : t > kScoreTokensPerBlock  ? kScoreTokensPerBlock
+                                           : t);
 }
 inline int score_blocks(const Dims& d) {
   const int tpb = score_tokens_per_block(d);
@@ -50,10 +59,12 @@ inline size_t topk_hist_bytes(const Dims& d) {
   return align_up(sizeof(int32_t) * (size_t)d.B * d.n_sets * kTopkBins);
 }
 
-// logits [B][L_max][H_r] fp32 + per-block (max, sum) [B][n_blk][H_r][2] fp32
-// + the top-k histogram of the scores written.
+// logits [B][H_r][row stride] fp32 + per-block (max, sum) [B][H_r][n_blk][2]
+// fp32 + the top-k histogram of the scores written.  A head's logits row is a
+// whole number of 16-byte pieces, so that they are read as such for any L_max.
+inline int score_row_stride(const Dims& d) { return (d.L_max + 3) / 4 * 4; }
 inline size_t score_logits_bytes(const Dims& d) {
-  return align_up(sizeof(float) * (size_t)d.B * d.L_max * d.H_r);
+  return align_up(sizeof(float) * (size_t)d.B * score_row_stride(d) * d.H_r);
 }
 inline size_t score_part_bytes(const Dims& d) {
   return align_up(sizeof(float) * 2 * (size_t)d.B * score_blocks(d) * d.H_r);

@@ -33,14 +33,14 @@ constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 
 struct RowArgs {
-  const float* logits;  // [B][H_r][L_max], log2 units; null: the scores are given
+  const float* logits;  // [B][H_r][ld], log2 units; null: the scores are given
   const float* part;    // [B][H_r][n_blk][2] per-block (max, sum exp2)
   float* scores;        // [B * n_sets][L_max]: written from the logits (null: not kept), or read
   const int32_t* seq_lens;
   const int32_t* ks;
   int32_t* idx;     // [B * n_sets][k_max]
   int32_t* counts;  // [B] or null
-  int L_max, k_max, H_r, n_sets, n_blk, tpb;
+  int L_max, ld, k_max, H_r, n_sets, n_blk, tpb;
 };
 
 template <bool kFromLogits>
@@ -72,10 +72,9 @@ __global__ __launch_bounds__(kThreads) void row_select_kernel(RowArgs a) {
   if (kFromLogits) {
     head_norm_finish(nrm, (L_b + a.tpb - 1) / a.tpb, s_c, s_wred);  // ends with a barrier
     const bool sum_heads = a.n_sets == 1;
-    const float* lg = a.logits + ((size_t)b * a.H_r + h0) * a.L_max;  // the row's first head
+    const float* lg = a.logits + ((size_t)b * a.H_r + h0) * a.ld;  // the row's first head
     float* keep = a.scores ? a.scores + (size_t)srow * a.L_max : nullptr;
-    const bool vec = (a.L_max & 3) == 0;
-    const bool vec_keep = vec && (reinterpret_cast<uintptr_t>(a.scores) & 15) == 0;
+    const bool vec_keep = (a.L_max & 3) == 0 && (reinterpret_cast<uintptr_t>(a.scores) & 15) == 0;
     for (int t0 = 4 * tid; t0 < a.L_max; t0 += 4 * kThreads) {
       float sc[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
       if (t0 < L_b) {
@@ -83,17 +82,12 @@ __global__ __launch_bounds__(kThreads) void row_select_kernel(RowArgs a) {
 #pragma unroll
         for (int h = 0; h < 16; ++h) {
           if (h < per) {
-            const float* l = lg + (size_t)h * a.L_max;
-            if (vec && t0 + 3 < a.L_max) {
-              const float4 v = *reinterpret_cast<const float4*>(l + t0);
-              lv[0][h] = v.x;
-              lv[1][h] = v.y;
-              lv[2][h] = v.z;
-              lv[3][h] = v.w;
-            } else {  // row tail: clamped into the row; values past the length are unused
-#pragma unroll
-              for (int e = 0; e < 4; ++e) lv[e][h] = l[min(t0 + e, a.L_max - 1)];
-            }
+            // t0 + 3 < ld; values past the length are unused
+            const float4 v = *reinterpret_cast<const float4*>(lg + (size_t)h * a.ld + t0);
+            lv[0][h] = v.x;
+            lv[1][h] = v.y;
+            lv[2][h] = v.z;
+            lv[3][h] = v.w;
           }
         }
 #pragma unroll
@@ -225,7 +219,7 @@ hipError_t launch_row_select(const Dims& d, void* ws_score, float* scores,
                              int32_t* counts, hipStream_t s) {
   RowArgs a{ws_score ? score_ws_logits(ws_score) : nullptr,
             ws_score ? score_ws_part(d, ws_score) : nullptr,
-            scores, seq_lens, ks, idx, counts, d.L_max, d.k_max, d.H_r, d.n_sets,
+            scores, seq_lens, ks, idx, counts, d.L_max, score_row_stride(d), d.k_max, d.H_r, d.n_sets,
             score_blocks(d), score_tokens_per_block(d)};
   const dim3 grid((unsigned)(d.B * d.n_sets));
   if (ws_score)

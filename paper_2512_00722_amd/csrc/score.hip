@@ -5,8 +5,8 @@
 //  1. logits_kernel streams K_r once.  Each lane holds 8 bf16 of one
 //     (token, head) row slice in one 16-byte load; the d_r/8 lanes of a head
 //     reduce their partial dot products with cross-lane shuffles.  A
-//     workgroup covers 256 tokens (64 or 128 when the grid would not cover
-//     the CUs); it writes the logits (log2 units, the scale and log2(e)
+//     workgroup covers 64 to 256 tokens (score_tokens_per_block); it writes the
+//     logits (log2 units, the scale and log2(e)
 //     folded into q_r) and its per-head (max, sum exp2).
 //  2. softmax_headsum_kernel merges the per-block pairs into each head's
 //     normaliser c_h = M_h + log2 Z_h and writes
@@ -31,16 +31,17 @@ struct LogitsArgs {
   const uint16_t* q_r;
   const uint16_t* k_r;
   const int32_t* seq_lens;
-  float* logits;  // [B][H_r][L_max], log2 units
+  float* logits;  // [B][H_r][ld], log2 units
   float* part;    // [B][H_r][n_blk][2]: block max, block sum of exp2(l - max)
   int32_t* hist;  // [B][n_sets][4096] top-k histograms, zeroed here for the next kernel (or null)
   int64_t kr_stride_b;
-  int L_max, H_r, n_blk, n_sets;
+  int L_max, ld, H_r, n_blk, n_sets;
+  int tpb;        // tokens per workgroup, at most T1
   float qscale;   // scale_r * log2(e)
 };
 
 // LPH: lanes per head = d_r / 8; kUnroll: rows in flight per lane; T1:
-// tokens per workgroup.
+// most tokens per workgroup (its LDS).
 template <int LPH, int kUnroll, int T1>
 __global__ __launch_bounds__(256) void logits_kernel(LogitsArgs a) {
   constexpr int d_r = LPH * 8;
@@ -51,9 +52,9 @@ __global__ __launch_bounds__(256) void logits_kernel(LogitsArgs a) {
     int32_t* h = a.hist + (size_t)b * a.n_sets * kTopkBins;
     for (int i = threadIdx.x; i < a.n_sets * kTopkBins; i += 256) h[i] = 0;
   }
-  const int t_begin = blk * T1;
+  const int t_begin = blk * a.tpb;
   if (t_begin >= L_b) return;  // uniform for the workgroup
-  const int n_tok = min(T1, L_b - t_begin);
+  const int n_tok = min(a.tpb, L_b - t_begin);
 
   const int cpt = a.H_r * LPH;  // 16-byte chunks per token row
   const int tpi = 256 / cpt;    // tokens per pass of the workgroup
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(256) void logits_kernel(LogitsArgs a) {
     for (int e = threadIdx.x; e < n_tok * a.H_r; e += 256) {
       const int h = e / n_tok;
       const int i = e - h * n_tok;
-      __hip_atomic_store(&a.logits[((size_t)b * a.H_r + h) * a.L_max + t_begin + i],
+      __hip_atomic_store(&a.logits[((size_t)b * a.H_r + h) * a.ld + t_begin + i],
                          lg[i * 17 + h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -135,7 +136,7 @@ struct SoftArgs {
   const int32_t* seq_lens;
   float* scores;   // [B][n_sets][L_max]
   int32_t* hist;   // [B][n_sets][4096]: histogram of key bits 31..20 of the scores
-  int L_max, H_r, n_blk, n_sets;
+  int L_max, ld, H_r, n_blk, n_sets;  // ld: floats between heads of the logits, a multiple of 4
   int tpb;         // tokens per block of the logits kernel
 };
 
@@ -168,21 +169,16 @@ __global__ __launch_bounds__(256) void softmax_headsum_kernel(SoftArgs a) {
   const int H_r = a.H_r;
   const int tb = t0 + 4 * tid;
   float lv[4][16];
-  const bool vec = (a.L_max & 3) == 0 && tb + 3 < a.L_max;
+  const int tl = min(tb, a.ld - 4);  // clamped into the row; values past the length are unused
 #pragma unroll
   for (int h = 0; h < 16; ++h) {
     if (h < per) {
-      const float* l = a.logits + ((size_t)b * H_r + h0 + h) * a.L_max;  // head row
-      if (vec) {
-        const float4 v = *reinterpret_cast<const float4*>(l + tb);
-        lv[0][h] = v.x;
-        lv[1][h] = v.y;
-        lv[2][h] = v.z;
-        lv[3][h] = v.w;
-      } else {  // row tail: clamped into the row; values past the length are unused
-#pragma unroll
-        for (int e = 0; e < 4; ++e) lv[e][h] = l[min(tb + e, a.L_max - 1)];
-      }
+      const float4 v = *reinterpret_cast<const float4*>(
+          a.logits + ((size_t)b * H_r + h0 + h) * a.ld + tl);
+      lv[0][h] = v.x;
+      lv[1][h] = v.y;
+      lv[2][h] = v.z;
+      lv[3][h] = v.w;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) lv[e][h] = 0.f;
@@ -234,10 +230,10 @@ constexpr size_t logits_lds_reserve(int tpb) {
 
 template <int LPH>
 void logits_dispatch(dim3 g, int tpb, bool wide, const LogitsArgs& a, hipStream_t s) {
-  if (tpb == 256) {
+  if (tpb > 128) {
     if (wide) logits_kernel<LPH, kUnrollWide, 256><<<g, 256, logits_lds_reserve(256), s>>>(a);
     else logits_kernel<LPH, kUnrollNarrow, 256><<<g, 256, 0, s>>>(a);
-  } else if (tpb == 128) {
+  } else if (tpb > 64) {
     logits_kernel<LPH, kUnrollNarrow, 128><<<g, 256, 0, s>>>(a);
   } else {
     logits_kernel<LPH, kUnrollNarrow, 64><<<g, 256, 0, s>>>(a);
@@ -251,8 +247,9 @@ hipError_t launch_logits(const Dims& d, const uint16_t* q_r, const uint16_t* k_r
   const int n_blk = score_blocks(d);
   LogitsArgs la{q_r, k_r, seq_lens, score_ws_logits(ws), score_ws_part(d, ws),
                 zero_hist ? score_ws_hist(d, ws) : nullptr, d.kr_stride_b,
-                d.L_max, d.H_r, n_blk, d.n_sets, d.scale_r * kLog2e};
-  const int tpb = score_tokens_per_block(d);
+                d.L_max, score_row_stride(d), d.H_r, n_blk, d.n_sets, score_tokens_per_block(d),
+                d.scale_r * kLog2e};
+  const int tpb = la.tpb;
   const dim3 g1(n_blk, d.B);
   const bool wide = (int64_t)n_blk * d.B >= 2 * (int64_t)device_cu_count();
   if (d.d_r == 64)
@@ -268,7 +265,8 @@ hipError_t launch_score(const Dims& d, const uint16_t* q_r, const uint16_t* k_r,
   hipError_t e = launch_logits(d, q_r, k_r, seq_lens, ws, true, s);
   if (e != hipSuccess) return e;
   SoftArgs sa{score_ws_logits(ws), score_ws_part(d, ws), seq_lens, scores, score_ws_hist(d, ws),
-              d.L_max, d.H_r, score_blocks(d), d.n_sets, score_tokens_per_block(d)};
+              d.L_max, score_row_stride(d), d.H_r, score_blocks(d), d.n_sets,
+              score_tokens_per_block(d)};
   const dim3 g2((d.L_max + T2 - 1) / T2, d.B * d.n_sets);
   softmax_headsum_kernel<<<g2, 256, 0, s>>>(sa);
   return hipGetLastError();

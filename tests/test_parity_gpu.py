@@ -80,6 +80,33 @@ def test_score_strided_kr(dev):
         np.testing.assert_allclose(got[b, :int(seq[b])], want, rtol=SCORE_REL, atol=SCORE_ABS)
 
 
+# Blocks of 64 to 256 tokens, a multiple of 16, the last one partial, and row
+# lengths that are no multiple of 4 (B, L_max, H_r, d_r; tokens per block)
+BLOCK_CASES = [
+    (100, 1003, 8, 64),    # 208
+    (33, 2047, 16, 64),    # 144
+    (2, 63, 3, 128),       # 64: less than one block
+    (1, 16387, 1, 64),     # 64, 257 blocks
+    (40, 3001, 16, 128),   # 256
+    (600, 70, 8, 64),      # more sequences than blocks are wanted: 256
+]
+
+
+@pytest.mark.parametrize("case", BLOCK_CASES, ids=[str(c) for c in BLOCK_CASES])
+def test_score_blocks(dev, case):
+    B, L, H_r, d_r = case
+    announce(f"score blocks {case}")
+    g = torch.Generator(device=dev).manual_seed(B + L)
+    K_r = torch.randn((B, L, H_r, d_r), generator=g, device=dev).to(torch.bfloat16)
+    q_r = torch.randn((B, H_r, d_r), generator=g, device=dev).to(torch.bfloat16)
+    lens = [(L * (b % 5 + 1)) // 5 for b in range(B)]
+    got = spec.score(q_r, K_r, torch.tensor(lens, dtype=torch.int32, device=dev)).cpu().numpy()
+    for b in sorted({0, 1, B // 2, B - 1} & set(range(B))):
+        want = oracle.retrieval_scores(f64(q_r[b]), f64(K_r[b]), lens[b])
+        assert np.all(np.abs(got[b, :lens[b]] - want) <= SCORE_ABS + SCORE_REL * want), b
+        assert np.all(np.isneginf(got[b, lens[b]:]))
+
+
 # ------------------------------------------------------------------ top-k
 
 def _topk_rows(kind, B, L, g):
