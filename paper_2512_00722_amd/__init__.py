@@ -175,7 +175,7 @@ def load_library(path: Optional[str] = None):
             raise ImportError("the native binding has not been built: build it with `python -m "
                               "paper_2512_00722_amd.build` (or __graft_entry__.build())") from e
         fast.init(*(ctypes.cast(getattr(lib, name), P).value for name in _FAST_API))
-        _lib, _fast = lib, fast
+        _fast, _lib = fast, lib  # a thread that finds _lib finds _fast
     return lib
 
 

@@ -133,12 +133,21 @@ bool caches(const at::Tensor* K, const at::Tensor* V) {
 #define EXPECT(x) \
   if (!(x)) Py_RETURN_NONE
 
-template <class F>
-PyObject* call(F f) {
+// Calls f without the GIL.  The arguments, the tensors' pointers among them, are
+// evaluated by the caller, so no tensor is touched while other threads run; an
+// exception finds the GIL held again.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+template <class F, class... A>
+PyObject* call(F f, A... args) {
   spec_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = f();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked unlocked;
+    st = f(args...);
+  }
   return PyLong_FromLong((long)st);
 }
 
@@ -186,11 +195,8 @@ PyObject* fast_attn(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.kv_stride_b = K->stride(1);
   size_t need = 0;
   EXPECT(enough(d, SPEC_OP_ATTN, ws, &need));
-  return call([&] {
-    return api.attn(&d, ptr<uint16_t>(q), ptr<uint16_t>(K), ptr<uint16_t>(V), ptr<int32_t>(idx),
-                    ptr<int32_t>(counts), ptr<float>(out), ptr<float>(lse), ws->data_ptr(), need,
-                    stream);
-  });
+  return call(api.attn, &d, ptr<uint16_t>(q), ptr<uint16_t>(K), ptr<uint16_t>(V), ptr<int32_t>(idx),
+              ptr<int32_t>(counts), ptr<float>(out), ptr<float>(lse), ws->data_ptr(), need, stream);
 }
 
 // score(q_r, K_r, seq_lens, L_max|None, scale_r, out, ws, n_sets, stream)
@@ -227,10 +233,8 @@ PyObject* fast_score(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.kr_stride_b = K_r->stride(0);
   size_t need = 0;
   EXPECT(enough(d, SPEC_OP_SCORE, ws, &need));
-  return call([&] {
-    return api.score(&d, ptr<uint16_t>(q_r), ptr<uint16_t>(K_r), ptr<int32_t>(seq_lens),
-                     ptr<float>(out), ws->data_ptr(), need, stream);
-  });
+  return call(api.score, &d, ptr<uint16_t>(q_r), ptr<uint16_t>(K_r), ptr<int32_t>(seq_lens),
+              ptr<float>(out), ws->data_ptr(), need, stream);
 }
 
 // topk(scores, seq_lens, ks, k_max, idx, counts, ws, stream)
@@ -263,10 +267,8 @@ PyObject* fast_topk(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.H_q = d.H_kv = d.n_sets = (int32_t)n_sets;
   size_t need = 0;
   EXPECT(enough(d, SPEC_OP_TOPK, ws, &need));
-  return call([&] {
-    return api.topk(&d, ptr<float>(scores), ptr<int32_t>(seq_lens), ptr<int32_t>(ks),
-                    ptr<int32_t>(idx), ptr<int32_t>(counts), ws->data_ptr(), need, stream);
-  });
+  return call(api.topk, &d, ptr<float>(scores), ptr<int32_t>(seq_lens), ptr<int32_t>(ks),
+              ptr<int32_t>(idx), ptr<int32_t>(counts), ws->data_ptr(), need, stream);
 }
 
 // step(q_r, K_r, seq_lens, ks, q, K, V, k_max, L_max|None, scale_r, scale,
@@ -350,13 +352,11 @@ PyObject* fast_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.n_sets = sets ? (int32_t)H_kv : 1;
   size_t need = 0;
   EXPECT(enough(d, SPEC_OP_STEP, ws, &need));
-  return call([&] {
-    return api.step(&d, ptr<uint16_t>(q_r), ptr<uint16_t>(K_r), ptr<int32_t>(seq_lens),
-                    ptr<int32_t>(ks), ptr<uint16_t>(q), ptr<uint16_t>(K), ptr<uint16_t>(V),
-                    ptr<int32_t>(outs[0]), ptr<int32_t>(outs[1]), ptr<float>(outs[2]),
-                    ptr<float>(outs[3]), ptr<float>(outs[4]), elastic ? &el : nullptr,
-                    ws->data_ptr(), need, stream);
-  });
+  return call(api.step, &d, ptr<uint16_t>(q_r), ptr<uint16_t>(K_r), ptr<int32_t>(seq_lens),
+              ptr<int32_t>(ks), ptr<uint16_t>(q), ptr<uint16_t>(K), ptr<uint16_t>(V),
+              ptr<int32_t>(outs[0]), ptr<int32_t>(outs[1]), ptr<float>(outs[2]),
+              ptr<float>(outs[3]), ptr<float>(outs[4]), elastic ? &el : nullptr, ws->data_ptr(),
+              need, stream);
 }
 
 // retrieval_qk(tokens, pos, emb, w_q, w_k, K_r, rope_base, yarn_scale,
@@ -397,11 +397,9 @@ PyObject* fast_retrieval_qk(PyObject*, PyObject* const* args, Py_ssize_t n) {
   fe.hidden = (int32_t)hidden;
   size_t need = 0;
   EXPECT(enough(d, SPEC_OP_FRONTEND, ws, &need));
-  return call([&] {
-    return api.retrieval_qk(&d, &fe, ptr<int32_t>(tokens), ptr<int32_t>(pos), ptr<uint16_t>(emb),
-                            ptr<uint16_t>(w_q), ptr<uint16_t>(w_k), ptr<uint16_t>(q_r),
-                            ptr<uint16_t>(K_r), ws->data_ptr(), need, stream);
-  });
+  return call(api.retrieval_qk, &d, &fe, ptr<int32_t>(tokens), ptr<int32_t>(pos),
+              ptr<uint16_t>(emb), ptr<uint16_t>(w_q), ptr<uint16_t>(w_k), ptr<uint16_t>(q_r),
+              ptr<uint16_t>(K_r), ws->data_ptr(), need, stream);
 }
 
 // mla(q, ckv, w_uk, w_uv, idx, counts, scale, out, lse|None, ws, stream)
@@ -446,11 +444,9 @@ PyObject* fast_mla(PyObject*, PyObject* const* args, Py_ssize_t n) {
   size_t need = 0;
   EXPECT(api.mla_workspace_size(&d, &need) == SPEC_OK);
   EXPECT((size_t)ws->numel() * ws->element_size() >= need);
-  return call([&] {
-    return api.mla(&d, ptr<uint16_t>(q), ptr<uint16_t>(ckv), ptr<uint16_t>(w_uk),
-                   ptr<uint16_t>(w_uv), ptr<int32_t>(idx), ptr<int32_t>(counts), ptr<float>(out),
-                   ptr<float>(lse), ws->data_ptr(), need, stream);
-  });
+  return call(api.mla, &d, ptr<uint16_t>(q), ptr<uint16_t>(ckv), ptr<uint16_t>(w_uk),
+              ptr<uint16_t>(w_uv), ptr<int32_t>(idx), ptr<int32_t>(counts), ptr<float>(out),
+              ptr<float>(lse), ws->data_ptr(), need, stream);
 }
 
 // init(addresses of the entry points, in Api's order)
