@@ -318,11 +318,13 @@ SPEC_API spec_status spec_step_offload(const spec_dims* dm, const uint16_t* q_r,
 /* The fused decode step of spec_step without a workspace argument, for
  * callers that cannot allocate device memory (code under HIP graph capture,
  * serving loops that forbid allocation).  Arguments, outputs and errors are
- * those of spec_step.  The workspace is a static device array of
- * spec_step_noalloc_max_bytes() bytes (64 MiB) that every GPU the library
- * runs on holds from the first call until the process ends; the call itself
- * allocates nothing.  A step whose spec_workspace_size(SPEC_OP_STEP)
- * exceeds it returns SPEC_ERR_TOO_LARGE before any HIP call (the five
+ * those of spec_step.  The workspace is a static device array (72 MiB)
+ * that every GPU the library runs on holds from the first call until the
+ * process ends; the call itself allocates nothing.  Steps whose
+ * spec_workspace_size(SPEC_OP_STEP) is within spec_step_noalloc_max_bytes()
+ * (64 MiB), less what the launch plans of scoring and attention add to their
+ * plain layouts, are taken; a larger one
+ * returns SPEC_ERR_TOO_LARGE before any HIP call (the five
  * benchmark workloads need 0.3-53 MB with one set per sequence).  All calls
  * on one GPU share that GPU's array, which keeps the last call's contents
  * (no part of it needs to start zeroed): calls that overlap on one GPU
@@ -337,7 +339,7 @@ SPEC_API spec_status spec_step_noalloc(const spec_dims* dm, const uint16_t* q_r,
                               float* lse, float* scores_out, const spec_elastic* el,
                               spec_stream stream);
 
-/* Size in bytes of spec_step_noalloc's static scratch (per GPU).            */
+/* The workspace in bytes that spec_step_noalloc's static scratch always holds. */
 SPEC_API size_t spec_step_noalloc_max_bytes(void);
 
 /* Retrieval-head front end parameters (host struct).                        */

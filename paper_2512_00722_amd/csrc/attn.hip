@@ -1201,11 +1201,34 @@ int device_cu_count() {
   return n;
 }
 
+namespace {
+size_t partials_bytes(const Dims& d, int64_t n_split) {
+  const size_t rows = (size_t)d.n_layers * d.B * n_split * d.H_q;
+  return align_up(sizeof(float) * rows * d.d) + align_up(sizeof(float) * rows * 2);
+}
+}  // namespace
+
+// At least the nominal size: a program that sizes its workspace for its largest
+// batch also runs smaller ones, whose plan may need partials where the largest
+// one's needs none.
 size_t attn_ws_bytes(const Dims& d) {
   const AttnPlan pl = attn_plan(d);
-  if (pl.mode != kGlobalPartials) return 0;
-  const size_t rows = (size_t)d.n_layers * d.B * pl.n_split * d.H_q;
-  return align_up(sizeof(float) * rows * d.d) + align_up(sizeof(float) * rows * 2);
+  const size_t plan = pl.mode == kGlobalPartials ? partials_bytes(d, pl.n_split) : 0;
+  const size_t nominal = attn_ws_nominal(d);
+  return plan > nominal ? plan : nominal;
+}
+
+size_t attn_ws_nominal(const Dims& d) {
+  // units of 64 tokens where those of kMinSplitTokens would be fewer than 64
+  const int64_t groups = (int64_t)d.n_layers * d.B * d.H_kv * attn_col_groups(d);
+  const bool small = groups * ((d.k_max + kMinSplitTokens - 1) / kMinSplitTokens) < 64;
+  const int64_t ways = (kWaveSlots * kSlotUnits + groups - 1) / groups;
+  int64_t split = ((d.k_max + ways - 1) / ways + kChunk - 1) / kChunk * kChunk;
+  const int64_t least = small ? 64 : kMinSplitTokens;
+  if (split < least) split = least;
+  if (split > kMaxSplit) split = kMaxSplit;
+  const int64_t n_split = (d.k_max + split - 1) / split;
+  return n_split > 1 ? partials_bytes(d, n_split) : 0;
 }
 
 namespace {

@@ -72,6 +72,15 @@ inline size_t score_part_bytes(const Dims& d) {
 inline size_t score_ws_bytes(const Dims& d) {
   return score_logits_bytes(d) + score_part_bytes(d) + topk_hist_bytes(d);
 }
+// The same with unpadded logits rows and blocks of 256 tokens, halved (down to
+// 64) while there are fewer than one per CU.
+inline size_t score_ws_nominal(const Dims& d) {
+  int64_t tpb = kScoreTokensPerBlock;
+  while (tpb > kScoreTokensPerBlockMin && d.B * ((d.L_max + tpb - 1) / tpb) < kScoreCUs) tpb /= 2;
+  return align_up(sizeof(float) * (size_t)d.B * d.L_max * d.H_r) +
+         align_up(sizeof(float) * 2 * (size_t)d.B * ((d.L_max + tpb - 1) / tpb) * d.H_r) +
+         topk_hist_bytes(d);
+}
 // The regions of a score workspace: logits, per-block pairs, histogram.
 inline float* score_ws_logits(void* ws) { return static_cast<float*>(ws); }
 inline float* score_ws_part(const Dims& d, void* ws) {
@@ -111,6 +120,7 @@ inline size_t topk_ws_bytes(const Dims& d) { return topk_hist_bytes(d) + topk_li
 // Attention: the workspace for partial results (zero unless a selection is
 // split across workgroups).
 size_t attn_ws_bytes(const Dims& d);
+size_t attn_ws_nominal(const Dims& d);  // with one wavefront per unit throughout
 
 // Elastic loading: per sequence the list of (slot, token) copies, then per
 // sequence whether the attention loads its rows itself (the fused step).
@@ -152,9 +162,13 @@ struct MlaDims {
 size_t mla_ws_bytes(const MlaDims& d);
 
 // The allocation-free decode step keeps its workspace in a static device
-// array of this size (one per GPU, held until the process ends);
-// static_scratch() gives its device address on the current GPU.
+// array (one per GPU, held until the process ends); static_scratch() gives
+// its device address on the current GPU.  Steps are accepted by their nominal
+// workspace (score_ws_nominal, attn_ws_nominal), so that the shapes it takes
+// do not move with the launch plans; the array holds what the plans need
+// beyond that (at most 3.2 MB more over shapes at the limit).
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
+constexpr size_t kStaticScratchRoom = size_t(8) << 20;
 hipError_t static_scratch(void** out);
 
 // Compute units of the device the process first launches on, queried once

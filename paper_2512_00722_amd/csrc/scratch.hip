@@ -1,5 +1,5 @@
 // Device scratch of the allocation-free decode step (spec_step_noalloc): a
-// file-scope device array of kStaticScratchBytes that every GPU the library
+// file-scope device array of 72 MiB that every GPU the library
 // runs on holds until the process ends.  In host code the array's name is
 // only a stand-in; its device address on the current GPU is looked up once
 // per device with hipGetSymbolAddress and cached, and only that address is
@@ -10,7 +10,7 @@
 
 namespace spec {
 
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticScratchRoom];
 
 namespace {
 constexpr int kMaxDevices = 64;

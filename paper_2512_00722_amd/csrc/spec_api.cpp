@@ -600,7 +600,12 @@ spec_status spec_step_noalloc(const spec_dims* dm, const uint16_t* q_r, const ui
   spec_status st = check_step(dm, &d, q_r, k_r, seq_lens, ks, q, k_cache, v_cache, idx_out,
                               counts_out, out, lse, scores_out, el);
   if (st != SPEC_OK) return st;
-  if (ws_bytes_for(d, SPEC_OP_STEP) > spec::kStaticScratchBytes) return SPEC_ERR_TOO_LARGE;
+  const size_t need = ws_bytes_for(d, SPEC_OP_STEP);
+  const size_t nominal = need - spec::score_ws_bytes(d) + spec::score_ws_nominal(d) -
+                         spec::attn_ws_bytes(d) + spec::attn_ws_nominal(d);
+  if (nominal > spec::kStaticScratchBytes ||
+      need > spec::kStaticScratchBytes + spec::kStaticScratchRoom)
+    return SPEC_ERR_TOO_LARGE;
   if (debug_on() && (st = debug_lengths(d, seq_lens, ks, as_stream(stream))) != SPEC_OK) return st;
   void* ws = nullptr;  // the device address of this GPU's static scratch
   const hipError_t e = spec::static_scratch(&ws);

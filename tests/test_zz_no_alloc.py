@@ -64,3 +64,22 @@ def test_step_noalloc_matches_step(dev, elastic):
             assert torch.equal(st_a.n_changed, st_b.n_changed)
         ks = np.minimum(x["ks"].cpu().numpy(), x["seq_lens"].cpu().numpy())
         assert a["counts"].cpu().numpy().tolist() == ks.tolist()
+
+
+def test_step_noalloc_at_scratch_limit(dev):
+    """A step whose nominal workspace is just within 64 MiB and whose launch
+    plans add to it (blocks of the scoring, padded logits rows) is taken, and
+    the static scratch holds it."""
+    w = small_workload(B=7, L=47580, H_r=16, d_r=64, n_layers=1, H_q=8, H_kv=8, k=373)
+    announce(f"no-alloc step at the scratch limit: {w}")
+    x = generate(w, seed=5, device=dev)
+    args = (x["q_r"], x["K_r"], x["seq_lens"], x["ks"], x["q"], x["K"], x["V"])
+    ws = spec.workspace_size(spec.Dims.make(
+        B=w.B, L_cap=w.L_cap, L_max=w.L_cap, k_max=w.k, H_r=16, d_r=64, n_layers=1, H_q=8,
+        H_kv=8, d=w.d, n_sets=8), spec.OP_STEP)
+    assert 64 << 20 < ws < 72 << 20
+    a = spec.step_noalloc(*args, k_max=w.k, head_level=True, with_lse=True, with_scores=True)
+    b = spec.step(*args, k_max=w.k, head_level=True, with_lse=True, with_scores=True)
+    torch.cuda.synchronize()
+    for name in ("idx", "counts", "out", "lse", "scores"):
+        assert torch.equal(a[name], b[name]), name
