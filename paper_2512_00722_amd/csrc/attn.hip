@@ -1202,20 +1202,25 @@ int device_cu_count() {
 }
 
 namespace {
-size_t partials_bytes(const Dims& d, int64_t n_split) {
-  const size_t rows = (size_t)d.n_layers * d.B * n_split * d.H_q;
+// n: (layer, sequence, split)s
+size_t partials_bytes(const Dims& d, int64_t n) {
+  const size_t rows = (size_t)n * d.H_q;
   return align_up(sizeof(float) * rows * d.d) + align_up(sizeof(float) * rows * 2);
 }
 }  // namespace
 
-// At least the nominal size: a program that sizes its workspace for its largest
-// batch also runs smaller ones, whose plan may need partials where the largest
-// one's needs none.
+// At least the nominal size, and the most that the team kernel's splits take: a
+// program that sizes its workspace for its largest batch also runs smaller
+// ones, whose plan may need partials where the largest one's needs fewer.
 size_t attn_ws_bytes(const Dims& d) {
   const AttnPlan pl = attn_plan(d);
-  const size_t plan = pl.mode == kGlobalPartials ? partials_bytes(d, pl.n_split) : 0;
+  const int64_t lb = (int64_t)d.n_layers * d.B;
+  int64_t n = lb * ((d.k_max + 2 * kChunk - 1) / (2 * kChunk));
+  const int64_t team = 2 * kCUs / (d.H_kv * attn_col_groups(d));
+  if (n > team) n = team;
+  if (pl.mode == kGlobalPartials && n < lb * pl.n_split) n = lb * pl.n_split;
   const size_t nominal = attn_ws_nominal(d);
-  return plan > nominal ? plan : nominal;
+  return partials_bytes(d, n) > nominal ? partials_bytes(d, n) : nominal;
 }
 
 size_t attn_ws_nominal(const Dims& d) {
@@ -1228,7 +1233,7 @@ size_t attn_ws_nominal(const Dims& d) {
   if (split < least) split = least;
   if (split > kMaxSplit) split = kMaxSplit;
   const int64_t n_split = (d.k_max + split - 1) / split;
-  return n_split > 1 ? partials_bytes(d, n_split) : 0;
+  return n_split > 1 ? partials_bytes(d, (int64_t)d.n_layers * d.B * n_split) : 0;
 }
 
 namespace {
