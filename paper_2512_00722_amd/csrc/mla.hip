@@ -67,7 +67,8 @@ constexpr int kLSteps = kDC / 32;    // k-steps on the latent part (high + low)
 constexpr int kQT = 2 * kDC + kDR;   // absorbed query row: high, low, rotary
 constexpr int kVBlocks = kDC / 16;   // 16-dim blocks of O^T
 constexpr int kMMaxSplit = 2048;     // longest split (tokens per work unit)
-constexpr int kMMinSplit = 256;
+constexpr int kMMinSplit = 256;      // shortest split of a launch that fills the CUs
+constexpr int kMMinSplitSmall = 64;  // shortest split
 constexpr int kMMaxSplitCount = 16;  // splits per (layer, sequence); the merge holds 16 weights
 constexpr float kLazy = 8.f;         // log2 headroom of the lazy softmax reference
 
@@ -795,23 +796,16 @@ __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
   }
 }
 
-// Splits of the selection: enough work units for 256 CUs (a fixed target,
-// so that the workspace size does not depend on the device), 256..2048
-// tokens per unit, at most 16 units per (layer, sequence).
+// Splits of the selection, 1 to 16 of up to 2048 tokens.
 struct MlaPlan {
   int n_split, split_tokens, n_units, n_hg, n_items;
 };
 
-MlaPlan mla_plan(const MlaDims& d) {
-  constexpr int kTargetUnits = 256;
-  const int groups = d.n_layers * d.B * (d.H / 64);
+MlaPlan mla_plan_of(const MlaDims& d, int want, int min_split) {
   MlaPlan p;
-  const int want = groups >= kTargetUnits ? 1 : (kTargetUnits + groups - 1) / groups;
   int split = (d.k_max + want - 1) / want;
-  const int at_most_16 = (d.k_max + kMMaxSplitCount - 1) / kMMaxSplitCount;
-  split = split < at_most_16 ? at_most_16 : split;
   split = (split + kMChunk - 1) / kMChunk * kMChunk;
-  split = split < kMMinSplit ? kMMinSplit : split;
+  split = split < min_split ? min_split : split;
   split = split > kMMaxSplit ? kMMaxSplit : split;
   p.split_tokens = split;
   p.n_split = (d.k_max + split - 1) / split;
@@ -821,19 +815,75 @@ MlaPlan mla_plan(const MlaDims& d) {
   return p;
 }
 
+constexpr int kCUs = 256;  // fixed: the workspace size must not depend on the device
+
+// As many units as CUs or more, of at least 256 tokens.
+MlaPlan mla_base_plan(const MlaDims& d) {
+  const int groups = d.n_layers * d.B * (d.H / 64);
+  const int fill = groups >= kCUs ? 1 : (kCUs + groups - 1) / groups;
+  return mla_plan_of(d, fill < kMMaxSplitCount ? fill : kMMaxSplitCount, kMMinSplit);
+}
+
+// Launches of at least as many (layer, sequence, head group)s as CUs are not
+// split: their rounds even out over ragged selections (13 layers x 30 ragged
+// sequences, k = 2048: 498 us, split further 623).  The others take the split
+// that is estimated the shortest, in us, of those that are one round of the
+// CUs: ~6 to start and 0.05 a token; the output kernel merges a split in 0.1 +
+// 0.25 per layer of 128 heads, for each 8 sequences; a unit's partials are
+// written and read at 0.03.  Fitted to 1 to 61 layers, 1 to 32 sequences, k =
+// 300 to 2048.  The base plan gives small launches long units on few CUs, and
+// others a second round (288 units).  us per call, base plan -> this: 1 layer x
+// 128 heads, 1 x k=300 35.5 -> 27.5, 1 x k=1000 36.2 -> 31.2, 8 x k=1000 42.9 ->
+// 37.5, 30 ragged x k=2048 98 -> 73; 3 layers, 8 x k=2048 91 -> 68; 7 layers, 5
+// ragged x k=1000 103 -> 84; 13 layers, 2 x k=2048 164 -> 127; 61 layers, 1 x
+// k=2048 460 -> 426.  Units longer than the base plan's only where they still
+// take three quarters of the CUs: fewer leave ragged selections nothing to even
+// out with.  Other splits in two rounds are not taken (13 layers, 5 ragged x
+// k=2048, 3 splits instead of the base plan's 2: 188 against 162).
+MlaPlan mla_plan(const MlaDims& d) {
+  const MlaPlan base = mla_base_plan(d);
+  if (d.n_layers * d.B * (d.H / 64) >= kCUs) return base;
+  const double merge = 0.1 + 0.25 / 128 * d.n_layers * d.H;
+  auto cost = [&](const MlaPlan& p) {
+    const int rounds = (p.n_items + kCUs - 1) / kCUs;
+    return rounds * (6 + 0.05 * p.split_tokens) + merge * p.n_split * ((d.B + 7) / 8) +
+           0.03 * p.n_units * p.n_hg;
+  };
+  MlaPlan best = base;
+  double least = 0.98 * cost(base);  // within the estimate's error: the base plan
+  for (int want = 1; want <= kMMaxSplitCount; ++want) {
+    const MlaPlan p = mla_plan_of(d, want, kMMinSplitSmall);
+    if (p.n_split > kMMaxSplitCount || p.n_items > kCUs) continue;  // one round
+    if (p.split_tokens > base.split_tokens && p.n_items < kCUs * 3 / 4) continue;
+    if (cost(p) < least) {
+      best = p;
+      least = cost(p);
+    }
+  }
+  return best;
+}
+
 size_t qt_bytes(const MlaDims& d) {
   return align_up(sizeof(uint16_t) * (size_t)d.n_layers * d.B * d.H * kQT);
 }
-size_t part_acc_bytes(const MlaDims& d, int n_split) {
-  return align_up(sizeof(float) * (size_t)d.n_layers * d.B * n_split * d.H * kDC);
+size_t part_acc_bytes(const MlaDims& d, int n_units) {
+  return align_up(sizeof(float) * (size_t)n_units * d.H * kDC);
 }
 
 }  // namespace
 
 size_t mla_ws_bytes(const MlaDims& d) {
-  const int ns = mla_plan(d).n_split;
-  return qt_bytes(d) + part_acc_bytes(d, ns) +
-         align_up(sizeof(float) * (size_t)d.n_layers * d.B * ns * d.H * 2);
+  // At least the base plan's units and the most that one round of small splits
+  // takes: a workspace sized for a larger batch or selection covers smaller
+  // ones, whose splits may be more.
+  const int most = (d.k_max + kMMinSplitSmall - 1) / kMMinSplitSmall;
+  const int64_t all = (int64_t)d.n_layers * d.B * (most < kMMaxSplitCount ? most : kMMaxSplitCount);
+  const int round = kCUs / (d.H / 64);
+  int units = all < round ? (int)all : round;
+  if (units < mla_base_plan(d).n_units) units = mla_base_plan(d).n_units;
+  if (units < mla_plan(d).n_units) units = mla_plan(d).n_units;
+  return qt_bytes(d) + part_acc_bytes(d, units) +
+         align_up(sizeof(float) * (size_t)units * d.H * 2);
 }
 
 hipError_t launch_mla(const MlaDims& d, const uint16_t* q, const uint16_t* ckv,
@@ -852,7 +902,7 @@ hipError_t launch_mla(const MlaDims& d, const uint16_t* q, const uint16_t* ckv,
   a.qt = reinterpret_cast<uint16_t*>(base);
   base += qt_bytes(d);
   a.part_acc = reinterpret_cast<float*>(base);
-  base += part_acc_bytes(d, p.n_split);
+  base += part_acc_bytes(d, p.n_units);
   a.part_ml = reinterpret_cast<float*>(base);
   a.out = out;
   a.lse = lse;

@@ -127,6 +127,27 @@ def test_mla_kernel_forms(dev, case):
             assert np.abs(lse[layer, b][heads] - wl).max() <= TOL_ATTN, (layer, b)
 
 
+# (B, L, k_max, n_layers, H, counts): edges of the split choice: one token, one
+# and two splits of the shortest length and a remainder beside them, split counts
+# in between (11 of 96, 13 of 160), selections that end inside, at and before
+# a split, and a long selection in one split
+SPLIT_CASES = [
+    (1, 64, 1, 1, 64, [1]),
+    (1, 80, 64, 1, 64, [64]),
+    (2, 80, 65, 1, 64, [65, 64]),
+    (1, 140, 129, 1, 128, [129]),
+    (1, 1100, 1000, 1, 128, [1000]),
+    (4, 2100, 2048, 1, 128, [2048, 1920, 161, 160]),
+    (40, 900, 700, 4, 128, [700 - 17 * i for i in range(40)]),
+]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES,
+                         ids=[f"B{c[0]}_k{c[2]}_l{c[3]}" for c in SPLIT_CASES])
+def test_mla_splits(dev, case):
+    test_mla_kernel_forms(dev, case)
+
+
 def test_mla_strided_cache_and_repeat(dev):
     """A cache with padding between sequences and layers (strides from the
     tensor view) gives the same result as a packed one, bit for bit, and a
