@@ -836,10 +836,13 @@ MlaPlan mla_base_plan(const MlaDims& d) {
 // 128 heads, 1 x k=300 35.5 -> 27.5, 1 x k=1000 36.2 -> 31.2, 8 x k=1000 42.9 ->
 // 37.5, 30 ragged x k=2048 98 -> 73; 3 layers, 8 x k=2048 91 -> 68; 7 layers, 5
 // ragged x k=1000 103 -> 84; 13 layers, 2 x k=2048 164 -> 127; 61 layers, 1 x
-// k=2048 460 -> 426.  Units longer than the base plan's only where they still
-// take three quarters of the CUs: fewer leave ragged selections nothing to even
-// out with.  Other splits in two rounds are not taken (13 layers, 5 ragged x
-// k=2048, 3 splits instead of the base plan's 2: 188 against 162).
+// k=2048 460 -> 426.  Units longer than the base plan's on fewer than three
+// quarters of the CUs save its second round (units of up to 1024 tokens: 13
+// layers, 5 x k=300 139 -> 111, 5 ragged x k=1000 157 -> 147; 8 layers, 9 x
+// k=300 120 -> 98), but not above that (13 layers, 5 ragged x k=2048 162 -> 177)
+// or where it has none (13 layers, 1 x k=2048 121 -> 127).  Other splits in two
+// rounds are not taken (13 layers, 5 ragged x k=2048, 3 splits instead of the
+// base plan's 2: 188 against 162).
 MlaPlan mla_plan(const MlaDims& d) {
   const MlaPlan base = mla_base_plan(d);
   if (d.n_layers * d.B * (d.H / 64) >= kCUs) return base;
@@ -854,7 +857,9 @@ MlaPlan mla_plan(const MlaDims& d) {
   for (int want = 1; want <= kMMaxSplitCount; ++want) {
     const MlaPlan p = mla_plan_of(d, want, kMMinSplitSmall);
     if (p.n_split > kMMaxSplitCount || p.n_items > kCUs) continue;  // one round
-    if (p.split_tokens > base.split_tokens && p.n_items < kCUs * 3 / 4) continue;
+    if (p.split_tokens > base.split_tokens && p.n_items < kCUs * 3 / 4 &&
+        (base.n_items <= kCUs || p.split_tokens > 1024))
+      continue;
     if (cost(p) < least) {
       best = p;
       least = cost(p);

@@ -139,6 +139,7 @@ SPLIT_CASES = [
     (1, 1100, 1000, 1, 128, [1000]),
     (4, 2100, 2048, 1, 128, [2048, 1920, 161, 160]),
     (40, 900, 700, 4, 128, [700 - 17 * i for i in range(40)]),
+    (9, 400, 300, 8, 128, [300 - 30 * i for i in range(9)]),
 ]
 
 
