@@ -252,6 +252,74 @@ __device__ __forceinline__ void store_v_rows(const int* rc, const uint4 (&vr)[kV
   }
 }
 
+// The reference of the weights 2^(l - max): logits of -inf alone so far (max =
+// -inf) take a finite one, which keeps their weights 0.  Results over them (max
+// -inf, sum 0) then weigh nothing in a merge with others; a whole selection of
+// them is 0 / 0.
+__device__ __forceinline__ float finite_ref(float max) { return max == -INFINITY ? 0.f : max; }
+
+// One chunk's online softmax and O^T += V^T P^T.  sacc: its S^T tiles (lane
+// holds S[head r16][token 16t + 4kg + i]), c: its first token of the n_tok, V:
+// its V tile in LDS, which is no longer read on return.
+__device__ __forceinline__ void softmax_pv(const floatx4 (&sacc)[kTiles], const int c,
+                                           const int n_tok, const float scale_log2,
+                                           const uint16_t* V, const int r16, const int kg,
+                                           float& m_run, float& l_run, floatx4 (&acc)[8]) {
+  float sv[kTiles][4];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool valid = c + 16 * t + 4 * kg + i < n_tok;
+      sv[t][i] = valid ? sacc[t][i] * scale_log2 : -INFINITY;
+      mx = fmaxf(mx, sv[t][i]);
+    }
+  mx = xgroup_max(mx);
+  const float mn = fmaxf(m_run, mx);
+  const float ref = finite_ref(mn);
+  const float alpha = exp2f(m_run - ref);
+  float ls = 0.f;
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sv[t][i] = exp2f(sv[t][i] - ref);
+      ls += sv[t][i];
+    }
+  l_run = l_run * alpha + ls;
+  m_run = mn;
+#pragma unroll
+  for (int db = 0; db < 8; ++db) acc[db] *= alpha;
+
+  // O^T += V^T P^T on the matrix cores.  The k-slots 8kg..8kg+7 of a
+  // 32-token block are tokens 4kg..4kg+3 of its first tile and of its
+  // second tile: exactly the S^T entries this lane holds.
+  wave_sync_lds();
+#pragma unroll
+  for (int kb2 = 0; kb2 < kChunk / 32; ++kb2) {
+    float pv[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      pv[i] = sv[2 * kb2][i];
+      pv[4 + i] = sv[2 * kb2 + 1][i];
+    }
+    bf16x8 phi, plo;
+    split_bf16x8(pv, phi, plo);
+    const uint16_t* r0 = V + (32 * kb2 + 4 * kg + (r16 >> 2)) * kVPitch + 4 * (r16 & 3);
+    const uint16_t* r1 = r0 + 16 * kVPitch;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      const bf16x4 va = lds_read_tr(r0 + 16 * db);
+      const bf16x4 vb4 = lds_read_tr(r1 + 16 * db);
+      const bf16x8 vA = __builtin_shufflevector(va, vb4, 0, 1, 2, 3, 4, 5, 6, 7);
+      acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vA, phi, acc[db], 0, 0, 0);
+      acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vA, plo, acc[db], 0, 0, 0);
+    }
+  }
+  wave_sync_lds();  // the V tile is rewritten by the next chunk
+}
+
 // A wavefront's tokens of one (layer, sequence, KV head) group, whose row
 // values are staged in `rows`: n_tok tokens, and one chunk of padding after
 // the last whole or partial chunk.  Local chunk c / kChunk holds the tokens
@@ -340,60 +408,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const int lb, const in
     load_k(c + kChunk, kraw);
     __builtin_amdgcn_sched_barrier(0);
 
-    float sv[kTiles][4];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool valid = c + 16 * t + 4 * kg + i < n_tok;
-        sv[t][i] = valid ? sacc[t][i] * a.scale_log2 : -INFINITY;
-        mx = fmaxf(mx, sv[t][i]);
-      }
-    mx = xgroup_max(mx);
-    const float mn = fmaxf(m_run, mx);
-    // logits of -inf alone so far: a finite reference keeps their weights 0
-    const float ref = mn == -INFINITY ? 0.f : mn;
-    const float alpha = exp2f(m_run - ref);
-    float ls = 0.f;
-#pragma unroll
-    for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sv[t][i] = exp2f(sv[t][i] - ref);
-        ls += sv[t][i];
-      }
-    l_run = l_run * alpha + ls;
-    m_run = mn;
-#pragma unroll
-    for (int db = 0; db < 8; ++db) acc[db] *= alpha;
-
-    // O^T += V^T P^T on the matrix cores.  The k-slots 8kg..8kg+7 of a
-    // 32-token block are tokens 4kg..4kg+3 of its first tile and of its
-    // second tile: exactly the S^T entries this lane holds.
-    wave_sync_lds();
-#pragma unroll
-    for (int kb2 = 0; kb2 < kChunk / 32; ++kb2) {
-      float pv[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        pv[i] = sv[2 * kb2][i];
-        pv[4 + i] = sv[2 * kb2 + 1][i];
-      }
-      bf16x8 phi, plo;
-      split_bf16x8(pv, phi, plo);
-      const uint16_t* r0 = V + (32 * kb2 + 4 * kg + (r16 >> 2)) * kVPitch + 4 * (r16 & 3);
-      const uint16_t* r1 = r0 + 16 * kVPitch;
-#pragma unroll
-      for (int db = 0; db < 8; ++db) {
-        const bf16x4 va = lds_read_tr(r0 + 16 * db);
-        const bf16x4 vb4 = lds_read_tr(r1 + 16 * db);
-        const bf16x8 vA = __builtin_shufflevector(va, vb4, 0, 1, 2, 3, 4, 5, 6, 7);
-        acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vA, phi, acc[db], 0, 0, 0);
-        acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vA, plo, acc[db], 0, 0, 0);
-      }
-    }
-    wave_sync_lds();  // the V tile is rewritten by the next chunk
+    softmax_pv(sacc, c, n_tok, a.scale_log2, V, r16, kg, m_run, l_run, acc);
   }
 }
 
@@ -586,7 +601,7 @@ void attn_team_kernel(AttnArgs a) {
   if (lane < kChunk) rows[kTeamRows + lane] = pad;
   wave_sync_lds();
 
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -INFINITY, l_run = -1.f;  // no tokens (a sum is never negative)
   floatx4 acc[8];
   if (n_tok > 0) {  // uniform per wavefront
     attend<KV>(a, lb, gv, kChunk * gw, NW, n_tok, rows, qf, V, lane, m_run, l_run, acc);
@@ -609,12 +624,13 @@ void attn_team_kernel(AttnArgs a) {
     const int h = hh - hs * G;
     float M = -INFINITY;
     for (int w = hs; w < W; w += a.team_heads) M = fmaxf(M, ml_lds[w][h].x);
+    const float ref = finite_ref(M);
     float L = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int w = hs; w < W; w += a.team_heads) {
       const float2 ml = ml_lds[w][h];
-      if (ml.x == -INFINITY && ml.y == 0.f) continue;  // no tokens: nothing was written
-      const float f = ml.x == M ? 1.f : exp2f(ml.x - M);
+      if (ml.y < 0.f) continue;  // no tokens: nothing was written
+      const float f = exp2f(ml.x - ref);
       const float4 x =
           reinterpret_cast<const float4*>(reinterpret_cast<const float*>(vlds[w]) + h * kMPitch)[d4];
       L += ml.y * f;
@@ -895,58 +911,7 @@ void attn_split_kernel(AttnArgs a) {
       load_k(rsrc, ksrc, kfsrc, kraw);
       __builtin_amdgcn_sched_barrier(0);
 
-      float sv[kTiles][4];
-      float mx = -INFINITY;
-#pragma unroll
-      for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool valid = c + 16 * t + 4 * kg + i < n_tok;
-          sv[t][i] = valid ? sacc[t][i] * a.scale_log2 : -INFINITY;
-          mx = fmaxf(mx, sv[t][i]);
-        }
-      mx = xgroup_max(mx);
-      const float mn = fmaxf(m_run, mx);
-      const float alpha = exp2f(m_run - mn);
-      float ls = 0.f;
-#pragma unroll
-      for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          sv[t][i] = exp2f(sv[t][i] - mn);
-          ls += sv[t][i];
-        }
-      l_run = l_run * alpha + ls;
-      m_run = mn;
-#pragma unroll
-      for (int db = 0; db < 8; ++db) acc[db] *= alpha;
-
-      // O^T += V^T P^T on the matrix cores.  The k-slots 8kg..8kg+7 of a
-      // 32-token block are tokens 4kg..4kg+3 of its first tile and of its
-      // second tile: exactly the S^T entries this lane holds.
-      wave_sync_lds();
-#pragma unroll
-      for (int kb2 = 0; kb2 < kChunk / 32; ++kb2) {
-        float pv[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          pv[i] = sv[2 * kb2][i];
-          pv[4 + i] = sv[2 * kb2 + 1][i];
-        }
-        bf16x8 phi, plo;
-        split_bf16x8(pv, phi, plo);
-        const uint16_t* r0 = V + (32 * kb2 + 4 * kg + (r16 >> 2)) * kVPitch + 4 * (r16 & 3);
-        const uint16_t* r1 = r0 + 16 * kVPitch;
-#pragma unroll
-        for (int db = 0; db < 8; ++db) {
-          const bf16x4 va = lds_read_tr(r0 + 16 * db);
-          const bf16x4 vb4 = lds_read_tr(r1 + 16 * db);
-          const bf16x8 vA = __builtin_shufflevector(va, vb4, 0, 1, 2, 3, 4, 5, 6, 7);
-          acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vA, phi, acc[db], 0, 0, 0);
-          acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vA, plo, acc[db], 0, 0, 0);
-        }
-      }
-      wave_sync_lds();  // the V tile is rewritten by the next chunk
+      softmax_pv(sacc, c, n_tok, a.scale_log2, V, r16, kg, m_run, l_run, acc);
     }
 
     // This unit's output: normalised (the whole selection) or a partial.
@@ -1051,7 +1016,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
       if (s0 + u * S < ns) Mb = fmaxf(Mb, ml[u].x);
-    const float r = exp2f(M - Mb);  // earlier batches onto the new maximum (0 at the first)
+    const float ref = finite_ref(Mb);
+    const float r = exp2f(M - ref);  // earlier batches onto the new maximum (0 at the first)
     L *= r;
     acc.x *= r;
     acc.y *= r;
@@ -1060,7 +1026,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       if (s0 + u * S < ns) {
-        const float w = exp2f(ml[u].x - Mb);
+        const float w = exp2f(ml[u].x - ref);
         L += ml[u].y * w;
         acc.x += pa[u].x * w;
         acc.y += pa[u].y * w;
@@ -1077,14 +1043,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
     if (part != 0 || h >= a.H_q) return;
     const int parts = min(S, ns);  // parts with a split
     for (int p = 1; p < parts; ++p) M = fmaxf(M, ml_lds[slot + p].x);
-    const float r = exp2f(ml_lds[slot].x - M);
+    const float ref = finite_ref(M);
+    const float r = exp2f(ml_lds[slot].x - ref);
     L *= r;
     acc.x *= r;
     acc.y *= r;
     acc.z *= r;
     acc.w *= r;
     for (int p = 1; p < parts; ++p) {
-      const float w = exp2f(ml_lds[slot + p].x - M);
+      const float w = exp2f(ml_lds[slot + p].x - ref);
       const float4 x = acc_lds[slot + p][d4];
       L += ml_lds[slot + p].y * w;
       acc.x += x.x * w;

@@ -342,6 +342,48 @@ def test_shared_units(dev, case):
         assert np.abs(lse[layer, b].cpu().numpy() - wl).max() <= TOL_ATTN
 
 
+# Selections that start with logits of -inf, by where those end: case, tokens.
+INF_CASES = [
+    # a wavefront's first chunks, in a direct shared unit and in a pipelined one
+    ((1, 100, 700, 8, 2, [(61 * b) % 521 for b in range(100)], 520), 40),
+    ((5, 32, 160, 32, 8, [(37 * b) % 129 for b in range(32)], 128), 40),
+    # whole splits: the only one of its part of the combine (48 parts of 128
+    # tokens, 8 of them in use), several of a part, and a pipelined one
+    ((1, 2, 6200, 8, 1, [1024, 0], 6144), 128),
+    ((1, 2, 6200, 8, 1, [6113, 2049], 6144), 4000),
+    ((1, 3, 20000, 8, 8, [16384, 0, 9001], 16384), 9000),
+]
+
+
+@pytest.mark.parametrize("case,drop", INF_CASES, ids=[str(c[:5]) + f"n{n}" for c, n in INF_CASES])
+def test_minus_infinity_logits(dev, case, drop, monkeypatch):
+    """Logits of -inf have weight 0 wherever they lie, whichever kernel runs;
+    a selection of nothing else has no weights (out NaN, lse -inf); cold and
+    pipelined units give the same bits."""
+    announce(f"attn -inf logits {case[:5]} {drop}")
+    g = torch.Generator().manual_seed(29 + sum(case[:5]))
+    q, K, V, idx, counts = _attn_inputs(case, g)
+    b = int(counts.argmax())                      # the longest selection
+    c = int(counts[b])
+    q[..., 0] = 1.0
+    K2 = K.clone()
+    K2[:, b, idx[b, :drop].long(), :, 0] = float("-inf")
+    args = (q.to(dev), K2.to(dev), V.to(dev), counts.to(dev))
+    out, lse = spec.sparse_decode_attn(*args, idx=idx.to(dev))
+    monkeypatch.setenv("SPEC_ATTN_SCHEDULE", "cold")
+    o2, l2 = spec.sparse_decode_attn(*args, idx=idx.to(dev))
+    monkeypatch.delenv("SPEC_ATTN_SCHEDULE")
+    assert torch.equal(out, o2) and torch.equal(lse, l2)
+    _check_attn(out[:, b:b + 1].cpu().numpy(), lse[:, b:b + 1].cpu().numpy(), q[:, b:b + 1],
+                K[:, b:b + 1], V[:, b:b + 1], idx[b:b + 1, drop:c], [c - drop], (case[0], 1))
+
+    K2[:, b, idx[b, :c].long(), :, 0] = float("-inf")
+    o3, l3 = spec.sparse_decode_attn(args[0], K2.to(dev), *args[2:], idx=idx.to(dev))
+    assert torch.isnan(o3[:, b]).all() and torch.isneginf(l3[:, b]).all()
+    rest = [i for i in range(case[1]) if i != b]
+    assert torch.equal(o3[:, rest], out[:, rest]) and torch.equal(l3[:, rest], lse[:, rest])
+
+
 # Pipelined launches over ragged batches with at least two (layer, sequence,
 # split) groups per workgroup on a 256-CU device (and at most 256
 # sequences): the groups are dealt to the workgroups by selection size.
