@@ -149,6 +149,32 @@ def test_mla_splits(dev, case):
     test_mla_kernel_forms(dev, case)
 
 
+@pytest.mark.parametrize("k,drop", [(1000, 64), (1000, 128), (1000, 700), (70, 40)])
+def test_mla_minus_infinity_logits(dev, k, drop):
+    """Rotary keys that give logits of -inf (weight 0): a first chunk of them,
+    whole splits at either end, and a whole selection (no weights: NaN)."""
+    announce(f"mla -inf logits k={k} drop={drop}")
+    w = small_workload(B=4, L=1100, k=k, n_layers=1, H_q=64, H_kv=1, mla=True)
+    x = generate_mla(w, seed=19, device=dev)
+    x["q_mla"][..., 128] = 1.0
+    counts = [k, k, k, 0]
+    idx = _random_idx(np.random.default_rng(23), 4, k, 1100, counts)
+    part = {0: idx[0, :drop], 1: idx[1, k - drop:k], 2: idx[2]}
+    for b, sel in part.items():
+        x["ckv"][:, b, torch.as_tensor(sel, device=dev).long(), 512] = float("-inf")
+    out, lse = spec.mla_sparse_decode_attn(
+        x["q_mla"], x["ckv"], x["w_uk"], x["w_uv"], torch.as_tensor(idx, device=dev),
+        torch.as_tensor(np.array(counts, dtype=np.int32), device=dev))
+    out, lse = out.cpu().numpy(), lse.cpu().numpy()
+    heads = np.array([0, 17, 63])
+    for b, sel in ((0, idx[0, drop:]), (1, idx[1, :k - drop])):
+        want, wl = _oracle(x, 0, b, sel, heads=heads)
+        assert np.abs(out[0, b][heads] - want).max() <= TOL_ATTN, b
+        assert np.abs(lse[0, b][heads] - wl).max() <= TOL_ATTN, b
+    assert np.isnan(out[0, 2]).all() and np.isneginf(lse[0, 2]).all()
+    assert np.all(out[0, 3] == 0) and np.isneginf(lse[0, 3]).all()
+
+
 def test_mla_strided_cache_and_repeat(dev):
     """A cache with padding between sequences and layers (strides from the
     tensor view) gives the same result as a packed one, bit for bit, and a
