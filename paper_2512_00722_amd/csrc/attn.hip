@@ -37,6 +37,7 @@
 // A unit that covers a whole selection normalises and writes out/lse itself;
 // split selections leave (max, sum, acc) partials that a second kernel merges
 // with a log-sum-exp combine.
+#include <float.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -252,11 +253,11 @@ __device__ __forceinline__ void store_v_rows(const int* rc, const uint4 (&vr)[kV
   }
 }
 
-// The reference of the weights 2^(l - max): logits of -inf alone so far (max =
-// -inf) take a finite one, which keeps their weights 0.  Results over them (max
-// -inf, sum 0) then weigh nothing in a merge with others; a whole selection of
-// them is 0 / 0.
-__device__ __forceinline__ float finite_ref(float max) { return max == -INFINITY ? 0.f : max; }
+// The running maximum before the first logit: below every finite one, and
+// finite itself, so that logits of -inf have weight 0 from the first chunk on
+// and results over nothing else (this maximum, sum 0) weigh nothing in a merge.
+// A whole selection of them is 0 / 0.
+constexpr float kNoMax = -FLT_MAX;
 
 // One chunk's online softmax and O^T += V^T P^T.  sacc: its S^T tiles (lane
 // holds S[head r16][token 16t + 4kg + i]), c: its first token of the n_tok, V:
@@ -277,14 +278,13 @@ __device__ __forceinline__ void softmax_pv(const floatx4 (&sacc)[kTiles], const 
     }
   mx = xgroup_max(mx);
   const float mn = fmaxf(m_run, mx);
-  const float ref = finite_ref(mn);
-  const float alpha = exp2f(m_run - ref);
+  const float alpha = exp2f(m_run - mn);
   float ls = 0.f;
 #pragma unroll
   for (int t = 0; t < kTiles; ++t)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      sv[t][i] = exp2f(sv[t][i] - ref);
+      sv[t][i] = exp2f(sv[t][i] - mn);
       ls += sv[t][i];
     }
   l_run = l_run * alpha + ls;
@@ -369,7 +369,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const int lb, const in
       vr[r] = ldkv(row_ptr<KV>(vb, vbf, rc[4 * r + kg], rs) + 8 * r16);
   };
 
-  m_run = -INFINITY;
+  m_run = kNoMax;
   l_run = 0.f;
 #pragma unroll
   for (int db = 0; db < 8; ++db) acc[db] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -624,13 +624,12 @@ void attn_team_kernel(AttnArgs a) {
     const int h = hh - hs * G;
     float M = -INFINITY;
     for (int w = hs; w < W; w += a.team_heads) M = fmaxf(M, ml_lds[w][h].x);
-    const float ref = finite_ref(M);
     float L = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int w = hs; w < W; w += a.team_heads) {
       const float2 ml = ml_lds[w][h];
       if (ml.y < 0.f) continue;  // no tokens: nothing was written
-      const float f = exp2f(ml.x - ref);
+      const float f = exp2f(ml.x - M);
       const float4 x =
           reinterpret_cast<const float4*>(reinterpret_cast<const float*>(vlds[w]) + h * kMPitch)[d4];
       L += ml.y * f;
@@ -870,7 +869,7 @@ void attn_split_kernel(AttnArgs a) {
     wave_sync_lds();
 
     const int n_tok = cur.n_tok;
-    float m_run = -INFINITY, l_run = 0.f;  // head r16
+    float m_run = kNoMax, l_run = 0.f;  // head r16
     floatx4 acc[8];                        // O^T[16db + 4kg + i][head r16]
 #pragma unroll
     for (int db = 0; db < 8; ++db) acc[db] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1016,8 +1015,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
       if (s0 + u * S < ns) Mb = fmaxf(Mb, ml[u].x);
-    const float ref = finite_ref(Mb);
-    const float r = exp2f(M - ref);  // earlier batches onto the new maximum (0 at the first)
+    const float r = exp2f(M - Mb);  // earlier batches onto the new maximum (0 at the first)
     L *= r;
     acc.x *= r;
     acc.y *= r;
@@ -1026,7 +1024,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       if (s0 + u * S < ns) {
-        const float w = exp2f(ml[u].x - ref);
+        const float w = exp2f(ml[u].x - Mb);
         L += ml[u].y * w;
         acc.x += pa[u].x * w;
         acc.y += pa[u].y * w;
@@ -1043,15 +1041,14 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
     if (part != 0 || h >= a.H_q) return;
     const int parts = min(S, ns);  // parts with a split
     for (int p = 1; p < parts; ++p) M = fmaxf(M, ml_lds[slot + p].x);
-    const float ref = finite_ref(M);
-    const float r = exp2f(ml_lds[slot].x - ref);
+    const float r = exp2f(ml_lds[slot].x - M);
     L *= r;
     acc.x *= r;
     acc.y *= r;
     acc.z *= r;
     acc.w *= r;
     for (int p = 1; p < parts; ++p) {
-      const float w = exp2f(ml_lds[slot + p].x - ref);
+      const float w = exp2f(ml_lds[slot + p].x - M);
       const float4 x = acc_lds[slot + p][d4];
       L += ml_lds[slot + p].y * w;
       acc.x += x.x * w;
