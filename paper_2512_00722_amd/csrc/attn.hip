@@ -221,6 +221,14 @@ __device__ __forceinline__ int elastic_row(int v, int slot, int L_cap) {
   if (KV != kKvElastic) return clampi(v, 0, L_cap - 1);
   return v >= 0 ? min(v, L_cap - 1) : -1 - slot;
 }
+// The row that padding reads (cache hits): row 0, or in elastic mode the unit's
+// first token (lane 0's staged value and slot), wherever that lies: its slot
+// may be one that this launch has yet to fill, and whatever it holds until then
+// would reach the output (0 x NaN).
+template <int KV>
+__device__ __forceinline__ int pad_row(int v, int slot, int L_cap) {
+  return KV == kKvElastic ? elastic_row<KV>(__builtin_amdgcn_readfirstlane(v), slot, L_cap) : 0;
+}
 template <int KV>
 __device__ __forceinline__ const uint16_t* row_ptr(const uint16_t* base, const uint16_t* buf,
                                                    int r, int64_t rs) {
@@ -461,13 +469,13 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
   bf16x8 qf[4];  // loaded together with the row indices
   load_q(a, lb, gv, lane, qf);
 
-  // Stage the rows of this item's tokens in LDS (masked tokens read row 0),
-  // so that no chunk waits on an index load from memory.
+  // Stage the rows of this item's tokens in LDS (masked tokens: the padding
+  // row), so that no chunk waits on an index load from memory.
   wave_sync_lds();  // the previous item's reads of rows/V are done
   {
     // All index loads are issued before any is used (one round trip), and
     // one chunk of padding follows the end: the software pipeline always
-    // prefetches the next chunk, and padding rows all read row 0 (cache hits).
+    // prefetches the next chunk, and its rows are all one (cache hits).
     const int32_t* idx_b =
         KV == kKvIndexed ? a.idx + ((size_t)b * a.n_sets + (a.n_sets > 1 ? g : 0)) * a.k_max + j0
         : KV == kKvElastic ? a.src + (size_t)b * a.k_max + j0
@@ -479,14 +487,15 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
 #pragma unroll
     for (int m = 0; m < kColdRowLoads; ++m) {
       const int j = lane + 64 * m;
-      rv[m] = KV == kKvElastic ? -1 : 0;  // padding: the unit's first slot, or row 0
+      rv[m] = KV == kKvElastic ? -1 : 0;
       if (j < n_tok && (KV != kKvElastic || fz)) rv[m] = KV == kKvCompact ? j0 + j : idx_b[j];
     }
+    const int pad = pad_row<KV>(rv[0], j0, a.L_cap);
 #pragma unroll
     for (int m = 0; m < kColdRowLoads; ++m) {
       const int j = lane + 64 * m;
       if (j < n_pad)
-        rows[j] = elastic_row<KV>(rv[m], j < n_tok ? j0 + j : j0, a.L_cap);
+        rows[j] = j < n_tok ? elastic_row<KV>(rv[m], j0 + j, a.L_cap) : pad;
     }
   }
   wave_sync_lds();
@@ -591,7 +600,7 @@ void attn_team_kernel(AttnArgs a) {
   const int mine = n_chunks > gw ? (n_chunks - gw + NW - 1) / NW : 0;
   const int n_tok = mine == 0 ? 0
                     : kChunk * mine - ((n_chunks - 1) % NW == gw ? kChunk * n_chunks - count : 0);
-  const int pad = KV == kKvElastic ? -1 - kChunk * gw : 0;  // its first slot, or row 0
+  const int pad = pad_row<KV>(fz ? rv[0] : -1, kChunk * gw, a.L_cap);
 #pragma unroll
   for (int m = 0; m < kLoads; ++m) {
     const int j = lane + 64 * m;
@@ -784,14 +793,13 @@ void attn_split_kernel(AttnArgs a) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) qraw[s] = ldg16(qp + 32 * s);
   };
-  // Rows of a unit's tokens into LDS: tokens past the unit, and the padding
-  // chunk, read row 0 (elastic mode: the unit's first slot; cache hits).
-  // Sets u.n_tok.
+  // Rows of a unit's tokens into LDS; tokens past the unit, and the padding
+  // chunk, read the padding row.  Sets u.n_tok.
   auto stage = [&](Unit& u, int* rows) {
     const int count = __builtin_amdgcn_readfirstlane(clampi(cnt_raw, 0, a.k_max));
     u.n_tok = min(a.split_tokens, count - u.j0);
-    const int pad = KV == kKvElastic ? -1 - u.j0 : 0;
     const bool fz = __builtin_amdgcn_readfirstlane(fz_raw) != 0;  // elastic: rows may come from the caches
+    const int pad = pad_row<KV>(fz ? rv[0] : -1, u.j0, a.L_cap);
 #pragma unroll
     for (int m = 0; m < kRowLoads; ++m) {
       const int j = lane + 64 * m;
@@ -879,7 +887,7 @@ void attn_split_kernel(AttnArgs a) {
     // Q.K^T MFMAs have read K(c); both stay in flight through the softmax and
     // the P.V MFMAs of chunk c.  Loads retire in issue order, so each wait is
     // a partial one.  After the last chunk the refill requests the next
-    // unit's first chunk, or padding rows (row 0, cache hits) if none follows.
+    // unit's first chunk, or padding rows (cache hits) if none follows.
     for (int c = 0; c < n_tok; c += kChunk) {
       const bool last = c + kChunk >= n_tok;
       const int* rsrc = last && chain ? rows_n : rows + c + kChunk;

@@ -698,6 +698,58 @@ def test_elastic_attention_loads_equal_copy(dev, kw, monkeypatch):
     assert torch.equal(st.kbuf, kb) and torch.equal(st.vbuf, vb)
 
 
+# Every form of the elastic attention, on selections that end inside a chunk:
+# (n_layers, B, L_cap, H_q, H_kv, counts, k_max)
+ELASTIC_FORMS = [
+    # workgroups that share a unit: one group each with four and eight
+    # wavefronts (18 and 200 groups), two groups each (400 groups), split with
+    # two groups each (64 groups), and the two column groups of a KV head, one of
+    # which writes, in one workgroup (96 groups)
+    (1, 9, 400, 8, 2, [0, 1, 31, 32, 33, 127, 128, 129, 200], 200),
+    (1, 100, 600, 4, 2, [(61 * b) % 521 for b in range(100)], 520),
+    (2, 50, 400, 8, 4, [(37 * b) % 201 for b in range(50)], 200),
+    (2, 50, 400, 8, 4, [(37 * b) % 301 for b in range(50)], 300),
+    (2, 4, 2100, 16, 8, [2048, 0, 1025, 63], 2048),
+    (1, 24, 700, 64, 2, [(103 * b) % 601 for b in range(24)], 600),
+    # one wavefront per unit: pipelined (1280 units), and split cold (960)
+    (5, 32, 160, 16, 8, [(37 * b) % 129 for b in range(32)], 128),
+    (4, 5, 1600, 8, 8, [1536, 1001, 0, 33, 257], 1536),
+]
+
+
+@pytest.mark.parametrize("case", ELASTIC_FORMS, ids=[str(c[:5]) + f"k{c[6]}" for c in ELASTIC_FORMS])
+def test_elastic_attention_unfilled_slots(dev, case):
+    """Slots that the attention is yet to fill hold NaN: the output and the
+    slots are those of the copy followed by compact attention, bit for bit,
+    after a full load and after one that keeps half of the rows."""
+    n_layers, B, L_cap, H_q, H_kv, counts, k_max = case
+    announce(f"elastic unfilled slots {case[:5]}")
+    g = torch.Generator(device=dev).manual_seed(41 + sum(case[:5]))
+    q, K, V = (torch.randn(s, generator=g, device=dev).to(torch.bfloat16)
+               for s in ((n_layers, B, H_q, 128),) + ((n_layers, B, L_cap, H_kv, 128),) * 2)
+    cnt = torch.tensor(counts, dtype=torch.int32, device=dev)
+    rng = np.random.default_rng(43 + sum(case[:5]))
+    st = spec.ElasticState(n_layers, B, k_max, H_kv, 128, dev)
+    keep = [np.zeros(0, dtype=np.int64)] * B
+    for it in range(2):
+        idx = np.full((B, k_max), -1, dtype=np.int32)
+        for b in range(B):
+            pool = np.setdiff1d(np.arange(L_cap), keep[b])
+            new = rng.choice(pool, counts[b] - len(keep[b]), replace=False)
+            idx[b, :counts[b]] = np.sort(np.concatenate([keep[b], new]))
+            keep[b] = idx[b, :counts[b]][rng.random(counts[b]) < 0.5].astype(np.int64)
+        spec.delta_gather(torch.as_tensor(idx, device=dev), cnt, K, V, st)
+        want = spec.sparse_decode_attn(q, st.kbuf, st.vbuf, cnt)
+        kb, vb = st.kbuf.clone(), st.vbuf.clone()
+        loaded = st.slot_src >= 0
+        assert bool(loaded.any())
+        st.kbuf[:, loaded] = float("nan")
+        st.vbuf[:, loaded] = float("nan")
+        got = spec.sparse_decode_attn_elastic(q, K, V, st, cnt)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), it
+        assert torch.equal(st.kbuf, kb) and torch.equal(st.vbuf, vb), it
+
+
 # ------------------------------------------------------- head-level selection
 
 SET_SCORE_CASES = [
