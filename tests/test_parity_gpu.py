@@ -698,6 +698,27 @@ def test_elastic_attention_loads_equal_copy(dev, kw, monkeypatch):
     assert torch.equal(st.kbuf, kb) and torch.equal(st.vbuf, vb)
 
 
+# The same on launches whose workgroups share a unit: split with two groups a
+# workgroup, direct with eight wavefronts and one group (200 groups) and two
+# (400), and the writer and the other column group of a KV head in one workgroup
+ELASTIC_TEAM_CASES = [
+    dict(B=4, L=2600, H_r=8, d_r=64, n_layers=2, H_q=16, H_kv=8, k=2040, heavy_frac=0.02,
+         ragged_min=900, extra_cap=8, steps=3),
+    dict(B=100, L=900, H_r=8, d_r=64, n_layers=1, H_q=4, H_kv=2, k=520, heavy_frac=0.02,
+         ragged_min=300, extra_cap=8, steps=3),
+    dict(B=50, L=700, H_r=8, d_r=64, n_layers=2, H_q=8, H_kv=4, k=300, heavy_frac=0.02,
+         ragged_min=200, extra_cap=8, steps=3),
+    dict(B=24, L=900, H_r=8, d_r=64, n_layers=1, H_q=64, H_kv=2, k=600, heavy_frac=0.02,
+         ragged_min=300, extra_cap=8, steps=3),
+]
+
+
+@pytest.mark.parametrize("kw", ELASTIC_TEAM_CASES,
+                         ids=[f"B{k['B']}k{k['k']}" for k in ELASTIC_TEAM_CASES])
+def test_elastic_shared_units_equal_copy(dev, kw, monkeypatch):
+    test_elastic_attention_loads_equal_copy(dev, kw, monkeypatch)
+
+
 # Every form of the elastic attention, on selections that end inside a chunk:
 # (n_layers, B, L_cap, H_q, H_kv, counts, k_max)
 ELASTIC_FORMS = [
