@@ -37,7 +37,11 @@
  *    not validated: L_b = min(seq_lens[b], L_max) (negative -> 0) and
  *    k_b = min(ks[b], L_b, k_max) (negative -> 0).
  *  - Ownership: the caller allocates every buffer, including the workspace
- *    sized by spec_workspace_size().  The library never allocates, frees or
+ *    sized by spec_workspace_size() for the call's dims (it does not grow with
+ *    every dimension: a launch over fewer sequences may leave more partial
+ *    results.  A workspace kept for several shapes is of the largest of their
+ *    sizes).  Smaller ones are taken as long as the plain launch plans fit,
+ *    which are slower.  The library never allocates, frees or
  *    synchronises; every call only enqueues work on `stream` (a hipStream_t,
  *    NULL = the null stream).  Outputs are valid once the stream reaches them.
  *  - Alignment: bf16 tensors, `out` and the workspace must be 16-byte
@@ -53,7 +57,8 @@
  *    two up to 128, H_kv > 16, n_sets not 1 or H_kv, n_sets = H_kv with H_r
  *    not a multiple of H_kv or B*n_sets > 65535, B or n_layers > 65535, and
  *    for elastic loading L_cap > 245760 or n_sets != 1.  SPEC_ERR_WORKSPACE: ws_bytes
- *    below spec_workspace_size() (SPEC_ERR_TOO_LARGE: above the static scratch
+ *    below what the plain launch plans take, and so below
+ *    spec_workspace_size() (SPEC_ERR_TOO_LARGE: above the static scratch
  *    of spec_step_noalloc).  SPEC_ERR_HIP: a launch failed; the HIP
  *    error code is kept (per thread) for spec_last_hip_error().
  *  - Calls are reentrant; concurrent calls must not share a workspace.

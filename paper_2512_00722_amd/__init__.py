@@ -119,9 +119,8 @@ class MlaDims(ctypes.Structure):
 _lib = None
 _fast = None  # native marshalling (binding/fast.cpp), loaded with the library
 # its entry points, in the order its init() takes their addresses
-_FAST_API = ["spec_workspace_size", "spec_score", "spec_topk", "spec_sparse_decode_attn",
-             "spec_step", "spec_retrieval_qk", "spec_mla_workspace_size",
-             "spec_mla_sparse_decode_attn"]
+_FAST_API = ["spec_score", "spec_topk", "spec_sparse_decode_attn", "spec_step",
+             "spec_retrieval_qk", "spec_mla_sparse_decode_attn"]
 
 
 def load_library(path: Optional[str] = None):
@@ -182,6 +181,8 @@ def load_library(path: Optional[str] = None):
 # ------------------------------------------------------------------ helpers
 
 def _check(st: int, where: str):
+    if st == 3:
+        raise ValueError(f"{where}: workspace too small")
     if st != 0:
         raise SpecError(st, where, _lib)
 
@@ -238,11 +239,11 @@ def workspace_size(dims: Dims, op: int) -> int:
 
 
 def _workspace(dims: Dims, op: int, device, ws: Optional[torch.Tensor]):
-    need = workspace_size(dims, op)
+    """(workspace, bytes): the caller's (the library decides whether it is
+    enough, see _check), or one of the size it asks for."""
     if ws is not None:
-        if ws.numel() * ws.element_size() < need:
-            raise ValueError(f"workspace too small: {need} bytes needed")
-        return ws, need
+        return ws, ws.numel() * ws.element_size()
+    need = workspace_size(dims, op)
     return torch.empty(max(need, 16), dtype=torch.uint8, device=device), need
 
 

@@ -25,13 +25,11 @@ namespace {
 
 // The C entry points, set once by init() from the loaded library.
 struct Api {
-  decltype(&spec_workspace_size) workspace_size;
   decltype(&spec_score) score;
   decltype(&spec_topk) topk;
   decltype(&spec_sparse_decode_attn) attn;
   decltype(&spec_step) step;
   decltype(&spec_retrieval_qk) retrieval_qk;
-  decltype(&spec_mla_workspace_size) mla_workspace_size;
   decltype(&spec_mla_sparse_decode_attn) mla;
 };
 Api api = {};
@@ -112,12 +110,6 @@ spec_dims base_dims() {
   return d;
 }
 
-// The workspace covers the call; *need: its size.
-bool enough(const spec_dims& d, spec_op op, const at::Tensor* ws, size_t* need) {
-  return api.workspace_size(&d, op, need) == SPEC_OK && ws &&
-         (size_t)ws->numel() * ws->element_size() >= *need;
-}
-
 // K and V caches of one shape and layout, the inner [token][head][dim] block dense.
 bool caches(const at::Tensor* K, const at::Tensor* V) {
   return is(K, at::kBFloat16, 5) && is(V, at::kBFloat16, 5) && K->sizes() == V->sizes() &&
@@ -193,10 +185,9 @@ PyObject* fast_attn(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.d = (int32_t)hd;
   d.kv_stride_layer = K->stride(0);
   d.kv_stride_b = K->stride(1);
-  size_t need = 0;
-  EXPECT(enough(d, SPEC_OP_ATTN, ws, &need));
   return call(api.attn, &d, ptr<uint16_t>(q), ptr<uint16_t>(K), ptr<uint16_t>(V), ptr<int32_t>(idx),
-              ptr<int32_t>(counts), ptr<float>(out), ptr<float>(lse), ws->data_ptr(), need, stream);
+              ptr<int32_t>(counts), ptr<float>(out), ptr<float>(lse), ws->data_ptr(),
+              ws->nbytes(), stream);
 }
 
 // score(q_r, K_r, seq_lens, L_max|None, scale_r, out, ws, n_sets, stream)
@@ -231,10 +222,8 @@ PyObject* fast_score(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.d_r = (int32_t)d_r;
   d.H_q = d.H_kv = d.n_sets = n_sets;
   d.kr_stride_b = K_r->stride(0);
-  size_t need = 0;
-  EXPECT(enough(d, SPEC_OP_SCORE, ws, &need));
   return call(api.score, &d, ptr<uint16_t>(q_r), ptr<uint16_t>(K_r), ptr<int32_t>(seq_lens),
-              ptr<float>(out), ws->data_ptr(), need, stream);
+              ptr<float>(out), ws->data_ptr(), ws->nbytes(), stream);
 }
 
 // topk(scores, seq_lens, ks, k_max, idx, counts, ws, stream)
@@ -265,10 +254,8 @@ PyObject* fast_topk(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.B = (int32_t)B;
   d.L_cap = d.L_max = (int32_t)L;
   d.H_q = d.H_kv = d.n_sets = (int32_t)n_sets;
-  size_t need = 0;
-  EXPECT(enough(d, SPEC_OP_TOPK, ws, &need));
   return call(api.topk, &d, ptr<float>(scores), ptr<int32_t>(seq_lens), ptr<int32_t>(ks),
-              ptr<int32_t>(idx), ptr<int32_t>(counts), ws->data_ptr(), need, stream);
+              ptr<int32_t>(idx), ptr<int32_t>(counts), ws->data_ptr(), ws->nbytes(), stream);
 }
 
 // step(q_r, K_r, seq_lens, ks, q, K, V, k_max, L_max|None, scale_r, scale,
@@ -350,13 +337,11 @@ PyObject* fast_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.kv_stride_layer = K->stride(0);
   d.kv_stride_b = K->stride(1);
   d.n_sets = sets ? (int32_t)H_kv : 1;
-  size_t need = 0;
-  EXPECT(enough(d, SPEC_OP_STEP, ws, &need));
   return call(api.step, &d, ptr<uint16_t>(q_r), ptr<uint16_t>(K_r), ptr<int32_t>(seq_lens),
               ptr<int32_t>(ks), ptr<uint16_t>(q), ptr<uint16_t>(K), ptr<uint16_t>(V),
               ptr<int32_t>(outs[0]), ptr<int32_t>(outs[1]), ptr<float>(outs[2]),
               ptr<float>(outs[3]), ptr<float>(outs[4]), elastic ? &el : nullptr, ws->data_ptr(),
-              need, stream);
+              ws->nbytes(), stream);
 }
 
 // retrieval_qk(tokens, pos, emb, w_q, w_k, K_r, rope_base, yarn_scale,
@@ -395,11 +380,9 @@ PyObject* fast_retrieval_qk(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.kr_stride_b = K_r->stride(0);
   fe.vocab = (int32_t)emb->size(0);
   fe.hidden = (int32_t)hidden;
-  size_t need = 0;
-  EXPECT(enough(d, SPEC_OP_FRONTEND, ws, &need));
   return call(api.retrieval_qk, &d, &fe, ptr<int32_t>(tokens), ptr<int32_t>(pos),
               ptr<uint16_t>(emb), ptr<uint16_t>(w_q), ptr<uint16_t>(w_k), ptr<uint16_t>(q_r),
-              ptr<uint16_t>(K_r), ws->data_ptr(), need, stream);
+              ptr<uint16_t>(K_r), ws->data_ptr(), ws->nbytes(), stream);
 }
 
 // mla(q, ckv, w_uk, w_uv, idx, counts, scale, out, lse|None, ws, stream)
@@ -441,12 +424,9 @@ PyObject* fast_mla(PyObject*, PyObject* const* args, Py_ssize_t n) {
   d.d_v = (int32_t)dv;
   d.ckv_stride_layer = ckv->stride(0);
   d.ckv_stride_b = ckv->stride(1);
-  size_t need = 0;
-  EXPECT(api.mla_workspace_size(&d, &need) == SPEC_OK);
-  EXPECT((size_t)ws->numel() * ws->element_size() >= need);
   return call(api.mla, &d, ptr<uint16_t>(q), ptr<uint16_t>(ckv), ptr<uint16_t>(w_uk),
               ptr<uint16_t>(w_uv), ptr<int32_t>(idx), ptr<int32_t>(counts), ptr<float>(out),
-              ptr<float>(lse), ws->data_ptr(), need, stream);
+              ptr<float>(lse), ws->data_ptr(), ws->nbytes(), stream);
 }
 
 // init(addresses of the entry points, in Api's order)

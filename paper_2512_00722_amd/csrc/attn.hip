@@ -1111,10 +1111,10 @@ int attn_col_groups(const Dims& d) { return d.G > 16 ? d.G / 16 : 1; }
 // against 26.6), with more than 512 groups, and for short selections of 256
 // groups or more (four chunks per wavefront).
 constexpr int kCUs = 256;  // fixed: the workspace size must not depend on the device
-// unit_tokens: tokens per unit of one wavefront each (attn_plan).
-bool team_plan(const Dims& d, int64_t groups, int64_t unit_tokens, AttnPlan* p) {
+// wave_splits: splits of a selection with one wavefront per unit (wave_plan).
+bool team_plan(const Dims& d, int64_t groups, int wave_splits, AttnPlan* p) {
   const int gu = d.H_kv * attn_col_groups(d);
-  const int64_t units = groups * ((d.k_max + unit_tokens - 1) / unit_tokens);
+  const int64_t units = groups * wave_splits;
   if (units <= kWaveSlots && units >= kWaveSlots / 16 * 15) return false;
   if (groups >= kCUs && d.k_max <= 4 * kChunk) return false;
   auto cost = [](int64_t wgs, int64_t tokens) { return tokens * (0.017 + 3e-5 * wgs); };
@@ -1145,18 +1145,26 @@ bool team_plan(const Dims& d, int64_t groups, int64_t unit_tokens, AttnPlan* p) 
   return best < 1e30;
 }
 
-AttnPlan attn_plan(const Dims& d) {
-  const int64_t base = (int64_t)d.n_layers * d.B * d.H_kv * attn_col_groups(d);
+// One wavefront per unit.  A launch whose units of kMinSplitTokens would not
+// reach one per four CUs (a single short layer) may go down to 64 tokens.
+AttnPlan wave_plan(const Dims& d, int64_t groups) {
   auto round_chunk = [](int64_t t) { return (t + kChunk - 1) / kChunk * kChunk; };
-  int64_t n_split = (kWaveSlots * kSlotUnits + base - 1) / base;
+  const bool small = groups * ((d.k_max + kMinSplitTokens - 1) / kMinSplitTokens) < kCUs / 4;
+  const int64_t least = small ? 64 : kMinSplitTokens;
+  int64_t n_split = (kWaveSlots * kSlotUnits + groups - 1) / groups;
   int64_t split = round_chunk((d.k_max + n_split - 1) / n_split);
-  if (split < kMinSplitTokens) split = kMinSplitTokens;
+  if (split < least) split = least;
   if (split > kMaxSplit) split = kMaxSplit;
-  AttnPlan team;
-  if (team_plan(d, base, split, &team)) return team;
   n_split = (d.k_max + split - 1) / split;
   if (n_split == 1) return {kDirect, 1, (int)round_chunk(d.k_max), 0, 1};
   return {kGlobalPartials, (int)n_split, (int)split, 0, 1};
+}
+
+AttnPlan attn_plan(const Dims& d) {
+  const int64_t groups = (int64_t)d.n_layers * d.B * d.H_kv * attn_col_groups(d);
+  const AttnPlan wave = wave_plan(d, groups);
+  AttnPlan team;
+  return !d.plain && team_plan(d, groups, wave.n_split, &team) ? team : wave;
 }
 
 }  // namespace
@@ -1173,39 +1181,20 @@ int device_cu_count() {
   return n;
 }
 
-namespace {
-// n: (layer, sequence, split)s
-size_t partials_bytes(const Dims& d, int64_t n) {
-  const size_t rows = (size_t)n * d.H_q;
-  return align_up(sizeof(float) * rows * d.d) + align_up(sizeof(float) * rows * 2);
-}
-}  // namespace
-
-// At least the nominal size, and the most that the team kernel's splits take: a
-// program that sizes its workspace for its largest batch also runs smaller
-// ones, whose plan may need partials where the largest one's needs fewer.
+// The larger of what the plan and the plain one (one wavefront per unit) take.
 size_t attn_ws_bytes(const Dims& d) {
-  const AttnPlan pl = attn_plan(d);
-  const int64_t lb = (int64_t)d.n_layers * d.B;
-  int64_t n = lb * ((d.k_max + 2 * kChunk - 1) / (2 * kChunk));
-  const int64_t team = 2 * kCUs / (d.H_kv * attn_col_groups(d));
-  if (n > team) n = team;
-  if (pl.mode == kGlobalPartials && n < lb * pl.n_split) n = lb * pl.n_split;
-  const size_t nominal = attn_ws_nominal(d);
-  return partials_bytes(d, n) > nominal ? partials_bytes(d, n) : nominal;
-}
-
-size_t attn_ws_nominal(const Dims& d) {
-  // units of 64 tokens where those of kMinSplitTokens would be fewer than 64
-  const int64_t groups = (int64_t)d.n_layers * d.B * d.H_kv * attn_col_groups(d);
-  const bool small = groups * ((d.k_max + kMinSplitTokens - 1) / kMinSplitTokens) < 64;
-  const int64_t ways = (kWaveSlots * kSlotUnits + groups - 1) / groups;
-  int64_t split = ((d.k_max + ways - 1) / ways + kChunk - 1) / kChunk * kChunk;
-  const int64_t least = small ? 64 : kMinSplitTokens;
-  if (split < least) split = least;
-  if (split > kMaxSplit) split = kMaxSplit;
-  const int64_t n_split = (d.k_max + split - 1) / split;
-  return n_split > 1 ? partials_bytes(d, (int64_t)d.n_layers * d.B * n_split) : 0;
+  Dims plain = d;
+  plain.plain = true;
+  size_t most = 0;
+  for (const Dims* e : {&d, (const Dims*)&plain}) {
+    const AttnPlan p = attn_plan(*e);
+    const size_t rows = (size_t)d.n_layers * d.B * p.n_split * d.H_q;
+    const size_t n = p.mode == kGlobalPartials ? align_up(sizeof(float) * rows * d.d) +
+                                                     align_up(sizeof(float) * rows * 2)
+                                               : 0;
+    if (n > most) most = n;
+  }
+  return most;
 }
 
 namespace {

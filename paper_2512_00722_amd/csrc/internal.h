@@ -16,6 +16,10 @@ struct Dims {
   int n_sets;  // token sets per sequence: 1 (summed heads) or H_kv (one per KV head)
   int64_t kr_stride_b, kv_stride_layer, kv_stride_b;
   float scale_r, scale;
+  // A faster launch plan may take more workspace than the plain one, which a
+  // call takes whose workspace is smaller than that: what a program sized for
+  // another call holds decides how fast this one runs, not whether.
+  bool plain;
 };
 
 // ---- workspace geometry (every region aligned to 256 bytes) -------------
@@ -117,10 +121,9 @@ inline size_t topk_lists_bytes(const Dims& d) {
 }
 inline size_t topk_ws_bytes(const Dims& d) { return topk_hist_bytes(d) + topk_lists_bytes(d); }
 
-// Attention: the workspace for partial results (zero unless a selection is
-// split across workgroups).
+// Attention: the workspace for partial results (zero where neither the plan nor
+// the plain one splits a selection across workgroups).
 size_t attn_ws_bytes(const Dims& d);
-size_t attn_ws_nominal(const Dims& d);  // with one wavefront per unit throughout
 
 // Elastic loading: per sequence the list of (slot, token) copies, then per
 // sequence whether the attention loads its rows itself (the fused step).
@@ -164,9 +167,9 @@ size_t mla_ws_bytes(const MlaDims& d);
 // The allocation-free decode step keeps its workspace in a static device
 // array (one per GPU, held until the process ends); static_scratch() gives
 // its device address on the current GPU.  Steps are accepted by their nominal
-// workspace (score_ws_nominal, attn_ws_nominal), so that the shapes it takes
-// do not move with the launch plans; the array holds what the plans need
-// beyond that (at most 3.2 MB more over shapes at the limit).
+// workspace (score_ws_nominal, the attention's plain plan), so that the shapes
+// it takes do not move with the launch plans; the array holds what the plans
+// need beyond that.
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
 constexpr size_t kStaticScratchRoom = size_t(8) << 20;
 hipError_t static_scratch(void** out);

@@ -74,6 +74,7 @@ spec_status resolve(const spec_dims* dm, spec::Dims* o) {
   if (o->kv_stride_layer < kv_row || o->kv_stride_layer % 8) return SPEC_ERR_INVALID;
   o->scale_r = dm->scale_r > 0.f ? dm->scale_r : 1.0f / sqrtf((float)dm->d_r);
   o->scale = dm->scale > 0.f ? dm->scale : 1.0f / sqrtf((float)dm->d);
+  o->plain = false;
   return SPEC_OK;
 }
 
@@ -111,8 +112,13 @@ size_t ws_bytes_for(const spec::Dims& d, spec_op op) {
   return 0;
 }
 
-spec_status check_ws(const spec::Dims& d, spec_op op, const void* ws, size_t ws_bytes) {
-  const size_t need = ws_bytes_for(d, op);
+// Takes the plain launch plans where the workspace does not hold the others.
+spec_status check_ws(spec::Dims* d, spec_op op, const void* ws, size_t ws_bytes) {
+  size_t need = ws_bytes_for(*d, op);
+  if (need > 0 && (!ws || ws_bytes < need || !aligned16(ws))) {
+    d->plain = true;
+    need = ws_bytes_for(*d, op);
+  }
   if (need == 0) return SPEC_OK;
   if (!ws || ws_bytes < need) return SPEC_ERR_WORKSPACE;
   if (!aligned16(ws)) return SPEC_ERR_INVALID;
@@ -466,7 +472,7 @@ spec_status spec_score(const spec_dims* dm, const uint16_t* q_r, const uint16_t*
   if (!q_r || !k_r || !seq_lens || !scores) return SPEC_ERR_INVALID;
   if (!aligned16(q_r) || !aligned16(k_r) || !aligned4(seq_lens) || !aligned4(scores))
     return SPEC_ERR_INVALID;
-  if ((st = check_ws(d, SPEC_OP_SCORE, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_SCORE, ws, ws_bytes)) != SPEC_OK) return st;
   if (debug_on() && (st = debug_lengths(d, seq_lens, nullptr, as_stream(stream))) != SPEC_OK)
     return st;
   return finish(
@@ -484,7 +490,7 @@ spec_status spec_topk(const spec_dims* dm, const float* scores, const int32_t* s
   if (!aligned4(scores) || !aligned4(seq_lens) || !aligned4(ks) || !aligned4(idx) ||
       (counts && !aligned4(counts)))
     return SPEC_ERR_INVALID;
-  if ((st = check_ws(d, SPEC_OP_TOPK, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_TOPK, ws, ws_bytes)) != SPEC_OK) return st;
   if (debug_on() && (st = debug_lengths(d, seq_lens, ks, as_stream(stream))) != SPEC_OK) return st;
   return finish(hip_status(spec::launch_topk(d, scores, seq_lens, ks, idx, counts, ws,
                                              as_stream(stream))),
@@ -520,7 +526,7 @@ spec_status spec_sparse_decode_attn(const spec_dims* dm, const uint16_t* q, cons
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned4(counts) ||
       !aligned16(out) || (idx && !aligned4(idx)) || (lse && !aligned4(lse)))
     return SPEC_ERR_INVALID;
-  if ((st = check_ws(d, SPEC_OP_ATTN, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_ATTN, ws, ws_bytes)) != SPEC_OK) return st;
   if (debug_on() && (st = debug_selection(d.B, d.k_max, d.n_sets, idx, counts, d.L_cap,
                                           as_stream(stream))) != SPEC_OK)
     return st;
@@ -540,7 +546,7 @@ spec_status spec_delta_gather(const spec_dims* dm, const int32_t* idx_now,
   if (!aligned4(idx_now) || !aligned4(counts) || !aligned16(k_cache) || !aligned16(v_cache))
     return SPEC_ERR_INVALID;
   if ((st = check_elastic(d, el)) != SPEC_OK) return st;
-  if ((st = check_ws(d, SPEC_OP_DELTA, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_DELTA, ws, ws_bytes)) != SPEC_OK) return st;
   if (debug_on() && (st = debug_selection(d.B, d.k_max, 1, idx_now, counts, d.L_cap,
                                           as_stream(stream))) != SPEC_OK)
     return st;
@@ -563,7 +569,7 @@ spec_status spec_sparse_decode_attn_elastic(const spec_dims* dm, const uint16_t*
       !aligned16(out) || (lse && !aligned4(lse)))
     return SPEC_ERR_INVALID;
   if ((st = check_elastic(d, el)) != SPEC_OK) return st;
-  if ((st = check_ws(d, SPEC_OP_ATTN, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_ATTN, ws, ws_bytes)) != SPEC_OK) return st;
   if (debug_on() &&
       ((st = debug_selection(d.B, d.k_max, 1, nullptr, counts, d.L_cap, as_stream(stream))) !=
            SPEC_OK ||
@@ -585,7 +591,7 @@ spec_status spec_step(const spec_dims* dm, const uint16_t* q_r, const uint16_t* 
   spec_status st = check_step(dm, &d, q_r, k_r, seq_lens, ks, q, k_cache, v_cache, idx_out,
                               counts_out, out, lse, scores_out, el);
   if (st != SPEC_OK) return st;
-  if ((st = check_ws(d, SPEC_OP_STEP, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_STEP, ws, ws_bytes)) != SPEC_OK) return st;
   if (debug_on() && (st = debug_lengths(d, seq_lens, ks, as_stream(stream))) != SPEC_OK) return st;
   return run_step(d, q_r, k_r, seq_lens, ks, q, k_cache, v_cache, idx_out, counts_out, out, lse,
                   scores_out, el, ws, as_stream(stream));
@@ -601,11 +607,12 @@ spec_status spec_step_noalloc(const spec_dims* dm, const uint16_t* q_r, const ui
                               counts_out, out, lse, scores_out, el);
   if (st != SPEC_OK) return st;
   const size_t need = ws_bytes_for(d, SPEC_OP_STEP);
-  const size_t nominal = need - spec::score_ws_bytes(d) + spec::score_ws_nominal(d) -
-                         spec::attn_ws_bytes(d) + spec::attn_ws_nominal(d);
-  if (nominal > spec::kStaticScratchBytes ||
-      need > spec::kStaticScratchBytes + spec::kStaticScratchRoom)
-    return SPEC_ERR_TOO_LARGE;
+  spec::Dims plain = d;
+  plain.plain = true;
+  const size_t nominal = ws_bytes_for(plain, SPEC_OP_STEP) - spec::score_ws_bytes(d) +
+                         spec::score_ws_nominal(d);
+  if (nominal > spec::kStaticScratchBytes) return SPEC_ERR_TOO_LARGE;
+  if (need > spec::kStaticScratchBytes + spec::kStaticScratchRoom) d.plain = true;
   if (debug_on() && (st = debug_lengths(d, seq_lens, ks, as_stream(stream))) != SPEC_OK) return st;
   void* ws = nullptr;  // the device address of this GPU's static scratch
   const hipError_t e = spec::static_scratch(&ws);
@@ -627,7 +634,7 @@ spec_status spec_offload_load(const spec_dims* dm, const int32_t* idx_now, const
   if (!aligned4(idx_now) || !aligned4(counts)) return SPEC_ERR_INVALID;
   if (copy_stream && !layer_ready) return SPEC_ERR_INVALID;
   if ((st = check_elastic(d, el)) != SPEC_OK) return st;
-  if ((st = check_ws(d, SPEC_OP_DELTA, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_DELTA, ws, ws_bytes)) != SPEC_OK) return st;
   HostKv hk;
   if ((st = resolve_host_kv(d, host, &hk)) != SPEC_OK) return st;
   const hipStream_t s = as_stream(stream);
@@ -662,7 +669,7 @@ spec_status spec_step_offload(const spec_dims* dm, const uint16_t* q_r, const ui
                        scores_out, el)) != SPEC_OK)
     return st;
   if (copy_stream && !layer_ready) return SPEC_ERR_INVALID;
-  if ((st = check_ws(d, SPEC_OP_OFFLOAD, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_OFFLOAD, ws, ws_bytes)) != SPEC_OK) return st;
   const int n_off = d.n_layers - n_dev_layers;
   spec::Dims d_off = d;   // the offloaded layers: the slot buffers and the host copy
   d_off.n_layers = n_off;
@@ -728,7 +735,7 @@ spec_status spec_retrieval_qk(const spec_dims* dm, const spec_frontend* fe,
   if (!aligned4(tokens) || !aligned4(pos) || !aligned16(emb) || !aligned16(w_q) ||
       !aligned16(w_k) || !aligned16(q_r) || !aligned16(k_r))
     return SPEC_ERR_INVALID;
-  if ((st = check_ws(d, SPEC_OP_FRONTEND, ws, ws_bytes)) != SPEC_OK) return st;
+  if ((st = check_ws(&d, SPEC_OP_FRONTEND, ws, ws_bytes)) != SPEC_OK) return st;
   if (debug_on()) {  // token ids the kernel would clamp into the table
     std::vector<int32_t> h;
     if (!d2h(h, tokens, (size_t)d.B, as_stream(stream))) return SPEC_ERR_HIP;

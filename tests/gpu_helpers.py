@@ -26,3 +26,16 @@ def f64(t: torch.Tensor) -> np.ndarray:
 def announce(msg: str):
     print(f"[case] {msg}", flush=True)
     sys.stdout.flush()
+
+
+def plain_attn_bytes(n_layers, B, H_q, H_kv, k_max) -> int:
+    """The least attention workspace: partial results with one wavefront per
+    unit (at most 1024 units of 256 to 2048 tokens, 64 where units of 256 would
+    be fewer than 64), in two regions of whole 256 bytes."""
+    ceil = lambda a, b: -(-a // b)
+    groups = n_layers * B * H_kv * max(1, H_q // H_kv // 16)
+    least = 64 if groups * ceil(k_max, 256) < 64 else 256
+    split = min(max(ceil(ceil(k_max, ceil(1024, groups)), 32) * 32, least), 2048)
+    n = ceil(k_max, split)
+    rows = n_layers * B * n * H_q
+    return 0 if n == 1 else ceil(rows * 512, 256) * 256 + ceil(rows * 8, 256) * 256

@@ -3,11 +3,13 @@ include/spec.h declares, and rejects bad arguments before any HIP call
 (fake pointers are never dereferenced because validation fails first)."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
 
 import paper_2512_00722_amd as spec
+from tests.gpu_helpers import plain_attn_bytes
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -135,6 +137,24 @@ def test_workspace_sizes(lib):
     assert lib.spec_workspace_size(ctypes.byref(d), 9, ctypes.byref(ctypes.c_size_t())) == 1
     # the front end's fp32 partial sums: up to 16 slices of [B][2 * H_r * d_r]
     assert sizes[spec.OP_FRONTEND][1] >= 16 * 2 * 2 * 8 * 64 * 4
+
+
+def test_attention_workspace_sizes(lib):
+    """The attention asks for no less than the plain plan takes, for no more
+    than twice that or a round of the chip's workgroups, and for nothing where
+    neither plan leaves partial results (the benchmark step: 32 layers of 8
+    sequences)."""
+    rng = random.Random(5)
+    for _ in range(3000):
+        H_kv, G = rng.randint(1, 16), 2 ** rng.randint(0, 7)
+        d = dict(B=int(2 ** rng.uniform(0, 8)), n_layers=int(2 ** rng.uniform(0, 6)),
+                 k_max=int(2 ** rng.uniform(0, 14)), H_kv=H_kv, H_q=H_kv * G)
+        plain = plain_attn_bytes(d["n_layers"], d["B"], d["H_q"], H_kv, d["k_max"])
+        _, n = ws_size(lib, good_dims(**d), spec.OP_ATTN)
+        partials = 512 // (H_kv * max(1, G // 16)) * d["H_q"] * 520 + 512
+        assert plain <= n <= max(plain, partials), d
+    bench = good_dims(B=8, n_layers=32, L_cap=32768, L_max=32768, k_max=2048)
+    assert ws_size(lib, bench, spec.OP_ATTN) == (0, 0)
 
 
 def test_entry_points_reject_before_hip(lib):
