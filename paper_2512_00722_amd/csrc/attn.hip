@@ -610,17 +610,20 @@ void attn_team_kernel(AttnArgs a) {
   if (lane < kChunk) rows[kTeamRows + lane] = pad;
   wave_sync_lds();
 
-  float m_run = -INFINITY, l_run = -1.f;  // no tokens (a sum is never negative)
+  float m_run = kNoMax, l_run = 0.f;
   floatx4 acc[8];
   if (n_tok > 0) {  // uniform per wavefront
     attend<KV>(a, lb, gv, kChunk * gw, NW, n_tok, rows, qf, V, lane, m_run, l_run, acc);
     l_run = xgroup_sum(l_run);
-    float* dst = reinterpret_cast<float*>(V) + r16 * kMPitch + 4 * kg;
+  } else {
 #pragma unroll
-    for (int db = 0; db < 8; ++db)
-      *reinterpret_cast<float4*>(dst + 16 * db) =
-          make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+    for (int db = 0; db < 8; ++db) acc[db] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
+  float* dst = reinterpret_cast<float*>(V) + r16 * kMPitch + 4 * kg;
+#pragma unroll
+  for (int db = 0; db < 8; ++db)
+    *reinterpret_cast<float4*>(dst + 16 * db) =
+        make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
   if (kg == 0) ml_lds[wave][r16] = make_float2(m_run, l_run);
   __syncthreads();
   if (a.mode == kGlobalPartials && split * P >= n_chunks) return;  // no tokens: no partial
@@ -637,7 +640,6 @@ void attn_team_kernel(AttnArgs a) {
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int w = hs; w < W; w += a.team_heads) {
       const float2 ml = ml_lds[w][h];
-      if (ml.y < 0.f) continue;  // no tokens: nothing was written
       const float f = exp2f(ml.x - M);
       const float4 x =
           reinterpret_cast<const float4*>(reinterpret_cast<const float*>(vlds[w]) + h * kMPitch)[d4];
