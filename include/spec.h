@@ -109,7 +109,9 @@ typedef enum spec_op {
   SPEC_OP_DELTA = 4,
   SPEC_OP_STEP = 5,
   SPEC_OP_FRONTEND = 6,
-  SPEC_OP_OFFLOAD = 7     /* spec_step_offload */
+  SPEC_OP_OFFLOAD = 7,    /* spec_step_offload */
+  SPEC_OP_STEP_NOALLOC = 8 /* spec_step_noalloc: what it counts a step as (the
+                             least workspace that spec_step takes for it)    */
 } spec_op;
 
 /* A hipStream_t handle; NULL selects the null stream. */
@@ -323,14 +325,15 @@ SPEC_API spec_status spec_step_offload(const spec_dims* dm, const uint16_t* q_r,
 /* The fused decode step of spec_step without a workspace argument, for
  * callers that cannot allocate device memory (code under HIP graph capture,
  * serving loops that forbid allocation).  Arguments, outputs and errors are
- * those of spec_step.  The workspace is a static device array (72 MiB)
+ * those of spec_step.  The workspace is a static device array (69 MiB)
  * that every GPU the library runs on holds from the first call until the
- * process ends; the call itself allocates nothing.  Steps whose
- * spec_workspace_size(SPEC_OP_STEP) is within spec_step_noalloc_max_bytes()
- * (64 MiB), less what the launch plans of scoring and attention add to their
- * plain layouts, are taken; a larger one
- * returns SPEC_ERR_TOO_LARGE before any HIP call (the five
- * benchmark workloads need 0.3-53 MB with one set per sequence).  All calls
+ * process ends; the call itself allocates nothing.  A step whose
+ * spec_workspace_size(SPEC_OP_STEP_NOALLOC) exceeds
+ * spec_step_noalloc_max_bytes() (64 MiB) returns SPEC_ERR_TOO_LARGE before
+ * any HIP call, and every other one is taken (that size is of the plain launch
+ * plans, so that it does not change with the faster ones, which the array has
+ * room for beyond the 64 MiB; the five benchmark workloads need 0.3-53 MB
+ * with one set per sequence).  All calls
  * on one GPU share that GPU's array, which keeps the last call's contents
  * (no part of it needs to start zeroed): calls that overlap on one GPU
  * (concurrent streams or threads) race and must be serialised by the
@@ -344,7 +347,8 @@ SPEC_API spec_status spec_step_noalloc(const spec_dims* dm, const uint16_t* q_r,
                               float* lse, float* scores_out, const spec_elastic* el,
                               spec_stream stream);
 
-/* The workspace in bytes that spec_step_noalloc's static scratch always holds. */
+/* The largest spec_workspace_size(SPEC_OP_STEP_NOALLOC) that spec_step_noalloc
+ * takes, in bytes.                                                          */
 SPEC_API size_t spec_step_noalloc_max_bytes(void);
 
 /* Retrieval-head front end parameters (host struct).                        */

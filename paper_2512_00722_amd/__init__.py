@@ -28,14 +28,15 @@ __all__ = [
     "step_noalloc_max_bytes", "Frontend",
     "retrieval_qk", "MlaDims", "mla_workspace_size", "mla_sparse_decode_attn",
     "OP_SCORE", "OP_TOPK", "OP_GATHER", "OP_ATTN", "OP_DELTA", "OP_STEP", "OP_FRONTEND",
-    "OP_OFFLOAD", "HostKv", "OffloadEvents", "offload_load", "step_offload",
+    "OP_OFFLOAD", "OP_STEP_NOALLOC", "HostKv", "OffloadEvents", "offload_load", "step_offload",
     "EXPORTED_SYMBOLS",
 ]
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 lib_path = os.path.join(_PKG, "libspecctx.so")
 
-OP_SCORE, OP_TOPK, OP_GATHER, OP_ATTN, OP_DELTA, OP_STEP, OP_FRONTEND, OP_OFFLOAD = range(8)
+(OP_SCORE, OP_TOPK, OP_GATHER, OP_ATTN, OP_DELTA, OP_STEP, OP_FRONTEND, OP_OFFLOAD,
+ OP_STEP_NOALLOC) = range(9)
 STATUS = {0: "SPEC_OK", 1: "SPEC_ERR_INVALID", 2: "SPEC_ERR_UNSUPPORTED",
           3: "SPEC_ERR_WORKSPACE", 4: "SPEC_ERR_HIP", 5: "SPEC_ERR_TOO_LARGE"}
 

@@ -28,6 +28,13 @@ __device__ __forceinline__ uint4 ldg16(const uint16_t* p) {
   return *reinterpret_cast<const uint4*>(p);
 }
 
+// Four floats in one 16-byte load from a 4-byte aligned address.
+__device__ __forceinline__ float4 read16(const float* p) {
+  typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+  const floatx4u v = *reinterpret_cast<const floatx4u*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
 // Streaming 16-byte load: data read once, hint the caches not to keep it.
 __device__ __forceinline__ uint4 ldg16_stream(const uint16_t* p) {
   const uint4* q = reinterpret_cast<const uint4*>(p);

@@ -42,6 +42,13 @@ constexpr int64_t kScoreCUs = 256;  // fixed: the workspace size must not depend
 constexpr int kSoftTokensPerBlock = 1024;
 
 inline int score_tokens_per_block(const Dims& d) {
+  if (d.plain) {  // 256, halved while there are fewer blocks than CUs
+    int tpb = kScoreTokensPerBlock;
+    while (tpb > kScoreTokensPerBlockMin &&
+           (int64_t)d.B * ((d.L_max + tpb - 1) / tpb) < kScoreCUs)
+      tpb /= 2;
+    return tpb;
+  }
   const int64_t total = (int64_t)d.B * d.L_max;
   const int64_t round = kScoreCUs * kScoreTokensPerBlock;
   const int64_t per_cu = total > 2 * round ? (total + round - 1) / round : 2;
@@ -65,8 +72,9 @@ inline size_t topk_hist_bytes(const Dims& d) {
 
 // logits [B][H_r][row stride] fp32 + per-block (max, sum) [B][H_r][n_blk][2]
 // fp32 + the top-k histogram of the scores written.  A head's logits row is a
-// whole number of 16-byte pieces, so that they are read as such for any L_max.
-inline int score_row_stride(const Dims& d) { return (d.L_max + 3) / 4 * 4; }
+// whole number of 16-byte pieces, so that they are read as such for any L_max
+// (read16 in device_common.h; the plain layout has no such padding).
+inline int score_row_stride(const Dims& d) { return d.plain ? d.L_max : (d.L_max + 3) / 4 * 4; }
 inline size_t score_logits_bytes(const Dims& d) {
   return align_up(sizeof(float) * (size_t)d.B * score_row_stride(d) * d.H_r);
 }
@@ -75,15 +83,6 @@ inline size_t score_part_bytes(const Dims& d) {
 }
 inline size_t score_ws_bytes(const Dims& d) {
   return score_logits_bytes(d) + score_part_bytes(d) + topk_hist_bytes(d);
-}
-// The same with unpadded logits rows and blocks of 256 tokens, halved (down to
-// 64) while there are fewer than one per CU.
-inline size_t score_ws_nominal(const Dims& d) {
-  int64_t tpb = kScoreTokensPerBlock;
-  while (tpb > kScoreTokensPerBlockMin && d.B * ((d.L_max + tpb - 1) / tpb) < kScoreCUs) tpb /= 2;
-  return align_up(sizeof(float) * (size_t)d.B * d.L_max * d.H_r) +
-         align_up(sizeof(float) * 2 * (size_t)d.B * ((d.L_max + tpb - 1) / tpb) * d.H_r) +
-         topk_hist_bytes(d);
 }
 // The regions of a score workspace: logits, per-block pairs, histogram.
 inline float* score_ws_logits(void* ws) { return static_cast<float*>(ws); }
@@ -166,12 +165,15 @@ size_t mla_ws_bytes(const MlaDims& d);
 
 // The allocation-free decode step keeps its workspace in a static device
 // array (one per GPU, held until the process ends); static_scratch() gives
-// its device address on the current GPU.  Steps are accepted by their nominal
-// workspace (score_ws_nominal, the attention's plain plan), so that the shapes
-// it takes do not move with the launch plans; the array holds what the plans
-// need beyond that.
+// its device address on the current GPU.  Steps are accepted by their plain
+// workspace, so that the shapes it takes do not move with the launch plans.
+// The array also holds what the plans take beyond it: partial results of the
+// attention's shared units, at most 512 / (H_kv R) rows of H_q heads (R column
+// groups of at most 16 heads, so 8192 results of 520 bytes, 4.3 MB), and at most
+// 0.5 MB of padding and block pairs of the scoring (a sequence takes 57 KB or
+// more of the 64 MiB, so there are at most 1170).
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
-constexpr size_t kStaticScratchRoom = size_t(8) << 20;
+constexpr size_t kStaticScratchRoom = size_t(5) << 20;
 hipError_t static_scratch(void** out);
 
 // Compute units of the device the process first launches on, queried once

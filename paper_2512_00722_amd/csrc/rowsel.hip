@@ -82,8 +82,8 @@ __global__ __launch_bounds__(kThreads) void row_select_kernel(RowArgs a) {
 #pragma unroll
         for (int h = 0; h < 16; ++h) {
           if (h < per) {
-            // t0 + 3 < ld; values past the length are unused
-            const float4 v = *reinterpret_cast<const float4*>(lg + (size_t)h * a.ld + t0);
+            // up to 3 floats past the row (the next one, or the block pairs): unused
+            const float4 v = read16(lg + (size_t)h * a.ld + t0);
             lv[0][h] = v.x;
             lv[1][h] = v.y;
             lv[2][h] = v.z;

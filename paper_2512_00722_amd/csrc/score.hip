@@ -136,7 +136,7 @@ struct SoftArgs {
   const int32_t* seq_lens;
   float* scores;   // [B][n_sets][L_max]
   int32_t* hist;   // [B][n_sets][4096]: histogram of key bits 31..20 of the scores
-  int L_max, ld, H_r, n_blk, n_sets;  // ld: floats between heads of the logits, a multiple of 4
+  int L_max, ld, H_r, n_blk, n_sets;  // ld: floats between heads of the logits
   int tpb;         // tokens per block of the logits kernel
 };
 
@@ -169,12 +169,13 @@ __global__ __launch_bounds__(256) void softmax_headsum_kernel(SoftArgs a) {
   const int H_r = a.H_r;
   const int tb = t0 + 4 * tid;
   float lv[4][16];
-  const int tl = min(tb, a.ld - 4);  // clamped into the row; values past the length are unused
+  // Threads past the row read its start, and its last one up to 3 floats beyond
+  // it (the next row, or the block pairs): values past the length are unused.
+  const int tl = tb < a.ld ? tb : 0;
 #pragma unroll
   for (int h = 0; h < 16; ++h) {
     if (h < per) {
-      const float4 v = *reinterpret_cast<const float4*>(
-          a.logits + ((size_t)b * H_r + h0 + h) * a.ld + tl);
+      const float4 v = read16(a.logits + ((size_t)b * H_r + h0 + h) * a.ld + tl);
       lv[0][h] = v.x;
       lv[1][h] = v.y;
       lv[2][h] = v.z;

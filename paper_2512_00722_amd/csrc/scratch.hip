@@ -1,5 +1,5 @@
 // Device scratch of the allocation-free decode step (spec_step_noalloc): a
-// file-scope device array of 72 MiB that every GPU the library
+// file-scope device array of 69 MiB that every GPU the library
 // runs on holds until the process ends.  In host code the array's name is
 // only a stand-in; its device address on the current GPU is looked up once
 // per device with hipGetSymbolAddress and cached, and only that address is

@@ -108,6 +108,11 @@ size_t ws_bytes_for(const spec::Dims& d, spec_op op) {
       return spec::align_up(sizeof(float) * (size_t)d.B * d.n_sets * d.L_max) +
              spec::score_ws_bytes(d) + spec::topk_ws_bytes(d) + attn_ws_any_layers(d) +
              spec::delta_ws_bytes(d);
+    case SPEC_OP_STEP_NOALLOC: {
+      spec::Dims plain = d;
+      plain.plain = true;
+      return ws_bytes_for(plain, SPEC_OP_STEP);
+    }
   }
   return 0;
 }
@@ -455,7 +460,7 @@ spec_status spec_mla_sparse_decode_attn(const spec_mla_dims* dm, const uint16_t*
 
 spec_status spec_workspace_size(const spec_dims* dm, spec_op op, size_t* bytes) {
   if (!bytes) return SPEC_ERR_INVALID;
-  if ((int)op < SPEC_OP_SCORE || (int)op > SPEC_OP_OFFLOAD) return SPEC_ERR_INVALID;
+  if ((int)op < SPEC_OP_SCORE || (int)op > SPEC_OP_STEP_NOALLOC) return SPEC_ERR_INVALID;
   spec::Dims d;
   const spec_status st = resolve(dm, &d);
   if (st != SPEC_OK) return st;
@@ -606,13 +611,9 @@ spec_status spec_step_noalloc(const spec_dims* dm, const uint16_t* q_r, const ui
   spec_status st = check_step(dm, &d, q_r, k_r, seq_lens, ks, q, k_cache, v_cache, idx_out,
                               counts_out, out, lse, scores_out, el);
   if (st != SPEC_OK) return st;
-  const size_t need = ws_bytes_for(d, SPEC_OP_STEP);
-  spec::Dims plain = d;
-  plain.plain = true;
-  const size_t nominal = ws_bytes_for(plain, SPEC_OP_STEP) - spec::score_ws_bytes(d) +
-                         spec::score_ws_nominal(d);
-  if (nominal > spec::kStaticScratchBytes) return SPEC_ERR_TOO_LARGE;
-  if (need > spec::kStaticScratchBytes + spec::kStaticScratchRoom) d.plain = true;
+  if (ws_bytes_for(d, SPEC_OP_STEP_NOALLOC) > spec::kStaticScratchBytes) return SPEC_ERR_TOO_LARGE;
+  if (ws_bytes_for(d, SPEC_OP_STEP) > spec::kStaticScratchBytes + spec::kStaticScratchRoom)
+    d.plain = true;
   if (debug_on() && (st = debug_lengths(d, seq_lens, ks, as_stream(stream))) != SPEC_OK) return st;
   void* ws = nullptr;  // the device address of this GPU's static scratch
   const hipError_t e = spec::static_scratch(&ws);

@@ -157,6 +157,50 @@ def test_attention_workspace_sizes(lib):
     assert ws_size(lib, bench, spec.OP_ATTN) == (0, 0)
 
 
+def plain_step_bytes(d):
+    """The least workspace of a step: scores, logits, block pairs (blocks of 256
+    tokens, halved while there are fewer than 256), two histograms, the
+    selection's lists, partial results, the elastic copy list."""
+    al = lambda n: -(-n // 256) * 256
+    B, L, H_r, rows = d["B"], d["L_max"], d["H_r"], d["B"] * d["n_sets"]
+    tpb = 256
+    while tpb > 64 and B * -(-L // tpb) < 256:
+        tpb //= 2
+    tiles = rows * -(-L // 2048)
+    return (al(4 * rows * L) + al(4 * B * L * H_r) + al(8 * B * -(-L // tpb) * H_r) +
+            2 * al(4 * rows * 4096) + al(16 * rows) + al(8 * tiles) + 3 * al(4 * tiles * 2048) +
+            plain_attn_bytes(d["n_layers"], B, d["H_q"], d["H_kv"], d["k_max"]) +
+            al(8 * B * d["k_max"]) + al(4 * B))
+
+
+def test_step_noalloc_is_predictable(lib):
+    """spec_step_noalloc takes a step exactly where the size that
+    spec_workspace_size gives for it is within its limit, whatever the launch
+    plans add; what they add fits beside the limit (5 MiB)."""
+    rng = random.Random(6)
+    args = [FAKE] * 10 + [None, None, None]
+    refused = 0
+    for _ in range(3000):
+        H_kv, G = rng.randint(1, 16), 2 ** rng.randint(0, 7)
+        L = int(2 ** rng.uniform(0, 18))
+        heads = rng.random() < 0.3
+        d = dict(B=int(2 ** rng.uniform(0, 9)), n_layers=int(2 ** rng.uniform(0, 5)), L_cap=L, L_max=L,
+                 k_max=min(L, int(2 ** rng.uniform(0, 14))), H_kv=H_kv, H_q=H_kv * G,
+                 H_r=H_kv if heads else rng.randint(1, 16), n_sets=H_kv if heads else 1)
+        dims = good_dims(**d)
+        st, n = ws_size(lib, dims, spec.OP_STEP_NOALLOC)
+        assert (st, n) == (0, plain_step_bytes(d)), d
+        _, n_step = ws_size(lib, dims, spec.OP_STEP)
+        assert n <= n_step, d
+        if n <= lib.spec_step_noalloc_max_bytes():
+            assert n_step <= n + (5 << 20), d
+        else:   # a call that is taken would use the fake pointers
+            refused += 1
+            assert lib.spec_step_noalloc(ctypes.byref(dims), *args, None) == 5, d
+    assert 100 < refused < 2900
+    assert lib.spec_last_hip_error() == 0
+
+
 def test_entry_points_reject_before_hip(lib):
     d = good_dims()
     _, nws = ws_size(lib, d, spec.OP_STEP)

@@ -7,7 +7,9 @@ import torch
 
 import oracle
 import paper_2512_00722_amd as spec
-from tests.gpu_helpers import TOL_ATTN, announce, f64, need_gpu, plain_attn_bytes
+from tests.gpu_helpers import (SCORE_ABS, SCORE_REL, TOL_ATTN, announce, f64, need_gpu,
+                               plain_attn_bytes)
+from workloads import generate, small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +69,56 @@ def test_attention_in_the_plain_workspace(dev, case):
     if need:
         with pytest.raises(ValueError):
             spec.sparse_decode_attn(q, K, V, cnt, idx=ix, ws=ws[:need - 16])
+
+
+# Lengths that leave the logits rows of the plain layout unaligned; one row kernel
+# per score row (short rows) and the tiled selection; blocks of 64, 128 and 256
+# tokens where the other plan takes fewer or more
+STEP_CASES = [
+    (dict(B=2, L=1003, H_r=8, d_r=64, n_layers=1, H_q=32, H_kv=8, k=500, ragged_min=3), False),
+    (dict(B=1, L=3, H_r=3, d_r=64, n_layers=1, H_q=4, H_kv=1, k=2), False),
+    (dict(B=3, L=20001, H_r=16, d_r=64, n_layers=1, H_q=16, H_kv=8, k=600, ragged_min=9000), True),
+    (dict(B=150, L=334, H_r=8, d_r=128, n_layers=1, H_q=8, H_kv=2, k=40, ragged_min=1), False),
+    (dict(B=40, L=9001, H_r=16, d_r=64, n_layers=1, H_q=4, H_kv=2, k=300, ragged_min=5000), False),
+]
+
+
+@pytest.mark.parametrize("kw,heads", STEP_CASES, ids=[f"B{k['B']}L{k['L']}" for k, _ in STEP_CASES])
+def test_step_in_the_plain_workspace(dev, kw, heads):
+    announce(f"step plain workspace {kw} heads={heads}")
+    w = small_workload(**kw)
+    x = generate(w, seed=kw["B"] + kw["L"], device=dev)
+    n_sets = w.H_kv if heads else 1
+    need = spec.workspace_size(spec.Dims.make(
+        B=w.B, L_cap=w.L_cap, L_max=w.L_cap, k_max=w.k, H_r=w.H_r, d_r=w.d_r, n_layers=w.n_layers,
+        H_q=w.H_q, H_kv=w.H_kv, d=w.d, n_sets=n_sets), spec.OP_STEP_NOALLOC)
+    ws, behind = _guarded(need, dev)
+    args = (x["q_r"], x["K_r"], x["seq_lens"], x["ks"], x["q"], x["K"], x["V"], w.k)
+    r = spec.step(*args, with_scores=True, with_lse=True, head_level=heads, ws=ws)
+    assert bool((behind == 0x5A).all())
+    idx, cnt = r["idx"].cpu().numpy(), r["counts"].cpu().numpy()
+    sc = r["scores"].cpu().numpy().astype(np.float64)
+    q, K, V = (f64(x[n]) for n in ("q", "K", "V"))
+    for b in {0, w.B // 2, w.B - 1}:
+        L = int(x["seq_lens"][b])
+        kb = min(int(x["ks"][b]), L)
+        assert cnt[b] == kb
+        qr, kr = f64(x["q_r"][b]), f64(x["K_r"][b])
+        want = (oracle.head_level_scores(qr, kr, L, n_sets) if heads
+                else oracle.retrieval_scores(qr, kr, L)[None])
+        got = sc[b] if heads else sc[b][None]
+        sets = idx[b] if heads else idx[b][None]
+        assert np.all(np.abs(got[:, :L] - want) <= SCORE_ABS + SCORE_REL * want), b
+        assert np.all(np.isneginf(got[:, L:])), b
+        for g in range(n_sets):
+            assert sets[g, :kb].tolist() == oracle.topk_indices(got[g, :L], kb).tolist(), (b, g)
+        if heads:
+            o, l = oracle.sparse_gqa_attention_sets(q[0, b], K[0, b], V[0, b],
+                                                    [s[:kb] for s in sets])
+        else:
+            o, l = oracle.sparse_gqa_attention(q[0, b], K[0, b], V[0, b], sets[0, :kb])
+        assert np.abs(r["out"][0, b].cpu().numpy() - o).max() <= TOL_ATTN, b
+        if kb:
+            assert np.abs(r["lse"][0, b].cpu().numpy() - l).max() <= TOL_ATTN, b
+    with pytest.raises(ValueError):
+        spec.step(*args, head_level=heads, ws=ws[:need - 16])

@@ -83,3 +83,22 @@ def test_step_noalloc_at_scratch_limit(dev):
     torch.cuda.synchronize()
     for name in ("idx", "counts", "out", "lse", "scores"):
         assert torch.equal(a[name], b[name]), name
+
+
+def test_step_noalloc_next_to_the_limit(dev):
+    """The same where the size that decides is within 0.1% of the limit, with
+    logits rows that the launch plan pads."""
+    w = small_workload(B=7, L=47581, H_r=16, d_r=64, n_layers=1, H_q=8, H_kv=8, k=373)
+    announce(f"no-alloc step next to the limit: {w}")
+    dims = spec.Dims.make(B=w.B, L_cap=w.L_cap, L_max=w.L_cap, k_max=w.k, H_r=16, d_r=64,
+                          n_layers=1, H_q=8, H_kv=8, d=w.d, n_sets=8)
+    limit = spec.step_noalloc_max_bytes()
+    assert 0.999 * limit < spec.workspace_size(dims, spec.OP_STEP_NOALLOC) <= limit
+    assert spec.workspace_size(dims, spec.OP_STEP) > limit
+    x = generate(w, seed=6, device=dev)
+    args = (x["q_r"], x["K_r"], x["seq_lens"], x["ks"], x["q"], x["K"], x["V"])
+    a = spec.step_noalloc(*args, k_max=w.k, head_level=True, with_lse=True, with_scores=True)
+    b = spec.step(*args, k_max=w.k, head_level=True, with_lse=True, with_scores=True)
+    torch.cuda.synchronize()
+    for name in ("idx", "counts", "out", "lse", "scores"):
+        assert torch.equal(a[name], b[name]), name
