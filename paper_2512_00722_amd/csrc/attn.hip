@@ -495,7 +495,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int item, 
     for (int m = 0; m < kColdRowLoads; ++m) {
       const int j = lane + 64 * m;
       if (j < n_pad)
-        rows[j] = j < n_tok ? elastic_row<KV>(rv[m], j0 + j, a.L_cap) : pad;
+        rows[j] = KV == kKvElastic && j >= n_tok ? pad : elastic_row<KV>(rv[m], j0 + j, a.L_cap);
     }
   }
   wave_sync_lds();
