@@ -444,7 +444,8 @@ typedef struct spec_mla_dims {
  * below the block it steps over or not a multiple of 8, a negative or
  * non-finite scale, non-zero reserved fields.  SPEC_ERR_UNSUPPORTED: other
  * widths than the ones above, H not 64 or 128, k_max > 32768, B > 65535.
- * SPEC_ERR_WORKSPACE: ws_bytes below spec_mla_workspace_size().             */
+ * SPEC_ERR_WORKSPACE: ws_bytes below what the plain launch plan takes, and so
+ * below spec_mla_workspace_size().                                          */
 SPEC_API spec_status spec_mla_sparse_decode_attn(const spec_mla_dims* dm, const uint16_t* q,
                                         const uint16_t* ckv, const uint16_t* w_uk,
                                         const uint16_t* w_uv, const int32_t* idx,

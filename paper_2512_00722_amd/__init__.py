@@ -819,17 +819,14 @@ def mla_sparse_decode_attn(q: torch.Tensor, ckv: torch.Tensor, w_uk: torch.Tenso
     dims = MlaDims.make(B=B, L_cap=L_cap, k_max=idx.shape[1], n_layers=n_layers, H=H, d_c=d_c,
                         d_rope=d_rope, d_nope=d_nope, d_v=d_v, ckv_stride_layer=ckv.stride(0),
                         ckv_stride_b=ckv.stride(1), scale=scale)
-    need = mla_workspace_size(dims)
     if ws is None:
-        ws = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-    elif ws.numel() * ws.element_size() < need:
-        raise ValueError(f"workspace too small: {need} bytes needed")
+        ws = torch.empty(mla_workspace_size(dims), dtype=torch.uint8, device=q.device)
     if out is None:
         out = torch.empty((n_layers, B, H, d_v), dtype=torch.float32, device=q.device)
     if lse is None and with_lse:
         lse = torch.empty((n_layers, B, H), dtype=torch.float32, device=q.device)
     _check(lib.spec_mla_sparse_decode_attn(ctypes.byref(dims), _p(q), _p(ckv), _p(w_uk),
                                            _p(w_uv), _p(idx), _p(counts), _p(out), _p(lse),
-                                           _p(ws), need, _stream(q)),
+                                           _p(ws), ws.numel() * ws.element_size(), _stream(q)),
            "spec_mla_sparse_decode_attn")
     return out, lse

@@ -160,6 +160,7 @@ struct MlaDims {
   int B, L_cap, k_max, n_layers, H;
   int64_t stride_layer, stride_b;  // elements between layers / sequences of the cache
   float scale;                     // resolved: 1/sqrt(d_nope + d_rope) by default
+  bool plain;                      // as Dims::plain
 };
 size_t mla_ws_bytes(const MlaDims& d);
 

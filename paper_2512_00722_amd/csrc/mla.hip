@@ -852,7 +852,7 @@ MlaPlan mla_base_plan(const MlaDims& d) {
 // base plan's 2: 188 against 162).
 MlaPlan mla_plan(const MlaDims& d) {
   const MlaPlan base = mla_base_plan(d);
-  if (d.n_layers * d.B * (d.H / 64) >= kCUs) return base;
+  if (d.plain || d.n_layers * d.B * (d.H / 64) >= kCUs) return base;
   const double merge = 0.1 + 0.25 / 128 * d.n_layers * d.H;
   auto cost = [&](const MlaPlan& p) {
     const int rounds = (p.n_items + kCUs - 1) / kCUs;
@@ -884,16 +884,10 @@ size_t part_acc_bytes(const MlaDims& d, int n_units) {
 
 }  // namespace
 
+// The larger of what the plan and the plain one (the base plan) take.
 size_t mla_ws_bytes(const MlaDims& d) {
-  // At least the base plan's units and the most that one round of small splits
-  // takes: a workspace sized for a larger batch or selection covers smaller
-  // ones, whose splits may be more.
-  const int most = (d.k_max + kMMinSplitSmall - 1) / kMMinSplitSmall;
-  const int64_t all = (int64_t)d.n_layers * d.B * (most < kMMaxSplitCount ? most : kMMaxSplitCount);
-  const int round = kCUs / (d.H / 64);
-  int units = all < round ? (int)all : round;
-  if (units < mla_base_plan(d).n_units) units = mla_base_plan(d).n_units;
-  if (units < mla_plan(d).n_units) units = mla_plan(d).n_units;
+  const int base = mla_base_plan(d).n_units, n = mla_plan(d).n_units;
+  const int units = base > n ? base : n;
   return qt_bytes(d) + part_acc_bytes(d, units) +
          align_up(sizeof(float) * (size_t)units * d.H * 2);
 }

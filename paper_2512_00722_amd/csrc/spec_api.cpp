@@ -347,6 +347,7 @@ spec_status resolve_mla(const spec_mla_dims* dm, spec::MlaDims* o) {
   if (o->stride_b < row || o->stride_b % 8) return SPEC_ERR_INVALID;
   if (o->stride_layer < row || o->stride_layer % 8) return SPEC_ERR_INVALID;
   o->scale = dm->scale > 0.f ? dm->scale : 1.0f / sqrtf((float)(dm->d_nope + dm->d_rope));
+  o->plain = false;
   return SPEC_OK;
 }
 
@@ -447,8 +448,8 @@ spec_status spec_mla_sparse_decode_attn(const spec_mla_dims* dm, const uint16_t*
   if (!aligned16(q) || !aligned16(ckv) || !aligned16(w_uk) || !aligned16(w_uv) ||
       !aligned4(idx) || !aligned4(counts) || !aligned16(out) || (lse && !aligned4(lse)))
     return SPEC_ERR_INVALID;
-  const size_t need = spec::mla_ws_bytes(d);
-  if (!ws || ws_bytes < need) return SPEC_ERR_WORKSPACE;
+  if (ws_bytes < spec::mla_ws_bytes(d)) d.plain = true;
+  if (!ws || ws_bytes < spec::mla_ws_bytes(d)) return SPEC_ERR_WORKSPACE;
   if (!aligned16(ws)) return SPEC_ERR_INVALID;
   if (debug_on() && (st = debug_selection(d.B, d.k_max, 1, idx, counts, d.L_cap,
                                           as_stream(stream))) != SPEC_OK)

@@ -9,7 +9,7 @@ import oracle
 import paper_2512_00722_amd as spec
 from tests.gpu_helpers import (SCORE_ABS, SCORE_REL, TOL_ATTN, announce, f64, need_gpu,
                                plain_attn_bytes)
-from workloads import generate, small_workload
+from workloads import generate, generate_mla, small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -122,3 +122,45 @@ def test_step_in_the_plain_workspace(dev, kw, heads):
             assert np.abs(r["lse"][0, b].cpu().numpy() - l).max() <= TOL_ATTN, b
     with pytest.raises(ValueError):
         spec.step(*args, head_level=heads, ws=ws[:need - 16])
+
+
+def plain_mla_bytes(n_layers, B, H, k_max):
+    """The least MLA workspace: absorbed queries and the partial results of
+    splits of 256 to 2048 tokens, at most 16 a sequence, that make 256 units."""
+    ceil = lambda a, b: -(-a // b)
+    al = lambda n: ceil(n, 256) * 256
+    split = ceil(ceil(k_max, min(16, ceil(256, n_layers * B * (H // 64)))), 32) * 32
+    units = n_layers * B * ceil(k_max, min(max(split, 256), 2048))
+    return al(2 * n_layers * B * H * (2 * 512 + 64)) + al(4 * units * H * 512) + al(8 * units * H)
+
+
+# Launches cut into more splits than the plain plan's, and into fewer
+@pytest.mark.parametrize("case", [(1, 1, 700, 128), (1, 4, 1000, 64), (8, 9, 300, 128)],
+                         ids=["l1_B1", "l1_B4", "l8_B9"])
+def test_mla_in_the_plain_workspace(dev, case):
+    n_layers, B, k, H = case
+    announce(f"mla plain workspace {case}")
+    w = small_workload(B=B, L=k + 50, k=k, n_layers=n_layers, H_q=H, H_kv=1, mla=True)
+    x = generate_mla(w, seed=29, device=dev)
+    counts = [k - 30 * b for b in range(B)]
+    rng = np.random.default_rng(31)
+    idx = np.full((B, k), -1, dtype=np.int32)
+    for b in range(B):
+        idx[b, :counts[b]] = np.sort(rng.choice(k + 50, counts[b], replace=False))
+    args = (x["q_mla"], x["ckv"], x["w_uk"], x["w_uv"], torch.as_tensor(idx, device=dev),
+            torch.tensor(counts, dtype=torch.int32, device=dev))
+    need = plain_mla_bytes(n_layers, B, H, k)
+    ws, behind = _guarded(need, dev)
+    out = torch.empty((n_layers, B, H, 128), device=dev)
+    for o in (out, None):   # native and ctypes marshalling
+        got, _ = spec.mla_sparse_decode_attn(*args, out=o, with_lse=False, ws=ws)
+        assert bool((behind == 0x5A).all())
+        for b in {0, B - 1}:
+            heads = [0, 17, H - 1]
+            q, c = f64(x["q_mla"][-1, b])[heads], f64(x["ckv"][-1, b])
+            want, _ = oracle.mla_sparse_attention(
+                q[:, :128], q[:, 128:], c[:, :512], c[:, 512:], f64(x["w_uk"][-1])[heads],
+                f64(x["w_uv"][-1])[heads], idx[b, :counts[b]])
+            assert np.abs(got[-1, b].cpu().numpy()[heads] - want).max() <= TOL_ATTN, b
+    with pytest.raises(ValueError):
+        spec.mla_sparse_decode_attn(*args, ws=ws[:need - 16])
