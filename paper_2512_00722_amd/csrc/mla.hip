@@ -647,7 +647,7 @@ void mla_attn_kernel(MlaArgs a) {
         *reinterpret_cast<float4*>(dst + 16 * db) =
             make_float4(acc[ht][db][0], acc[ht][db][1], acc[ht][db][2], acc[ht][db][3]);
       if (kg == 0) {
-        a.part_ml[prow * 2] = n_tok > 0 ? m_run[ht] : -INFINITY;
+        a.part_ml[prow * 2] = m_run[ht];
         a.part_ml[prow * 2 + 1] = l;
       }
     }
@@ -734,15 +734,11 @@ __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
       float M = -INFINITY;
       for (int s = 0; s < a.n_split; ++s) M = fmaxf(M, wml[s][tid].x);
       float L = 0.f;
-      for (int s = 0; s < a.n_split; ++s)
-        L += M == -INFINITY ? 0.f : exp2f(wml[s][tid].x - M) * wml[s][tid].y;
-      // M = -inf: an empty selection, output 0.  One of nothing but logits of
-      // -inf has a finite M and L = 0: no weights, output 0 / 0.
-      const float inv = M == -INFINITY ? 0.f : 1.f / L;
-      for (int s = 0; s < a.n_split; ++s) {
-        const float ms = wml[s][tid].x;
-        wsp[tid][s] = ms != -INFINITY ? exp2f(ms - M) * inv : 0.f;
-      }
+      for (int s = 0; s < a.n_split; ++s) L += exp2f(wml[s][tid].x - M) * wml[s][tid].y;
+      // no weights: an empty selection's output is 0, that of one of nothing but
+      // logits of -inf is 0 / 0
+      const float inv = L == 0.f && a.counts[b0 + tid] <= 0 ? 0.f : 1.f / L;
+      for (int s = 0; s < a.n_split; ++s) wsp[tid][s] = exp2f(wml[s][tid].x - M) * inv;
       wsp[tid][16] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
     }
     __syncthreads();
