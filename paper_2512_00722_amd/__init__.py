@@ -118,7 +118,7 @@ class MlaDims(ctypes.Structure):
 
 
 _lib = None
-_fast = None  # native marshalling (binding/fast.cpp), loaded with the library
+_fast = None  # native marshalling (binding/fast.cpp), loaded with the library if built
 # its entry points, in the order its init() takes their addresses
 _FAST_API = ["spec_score", "spec_topk", "spec_sparse_decode_attn", "spec_step",
              "spec_retrieval_qk", "spec_mla_sparse_decode_attn"]
@@ -171,10 +171,10 @@ def load_library(path: Optional[str] = None):
     if path is None:
         try:
             fast = importlib.import_module(__name__ + "._fast")
-        except ImportError as e:
-            raise ImportError("the native binding has not been built: build it with `python -m "
-                              "paper_2512_00722_amd.build` (or __graft_entry__.build())") from e
-        fast.init(*(ctypes.cast(getattr(lib, name), P).value for name in _FAST_API))
+        except ImportError:
+            fast = None  # not built: every call is marshalled through ctypes
+        else:
+            fast.init(*(ctypes.cast(getattr(lib, name), P).value for name in _FAST_API))
         _fast, _lib = fast, lib  # a thread that finds _lib finds _fast
     return lib
 
@@ -201,9 +201,10 @@ def _raw_stream(t: torch.Tensor) -> int:
 
 
 def _plain(t) -> bool:
-    """A device tensor proper: its call may take the native marshalling, which
-    falls back to the checks here (None) for anything unusual."""
-    return type(t) is torch.Tensor and t.is_cuda
+    """A device tensor proper: its call may take the native marshalling (where
+    that is built), which falls back to the checks here (None) for anything
+    unusual."""
+    return _fast is not None and type(t) is torch.Tensor and t.is_cuda
 
 
 def _need(t: torch.Tensor, name: str, dtype, ndim: int):

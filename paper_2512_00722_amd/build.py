@@ -68,20 +68,33 @@ def _compile(src: str) -> str:
 FAST_LIB = os.path.join(PKG, "_fast.so")
 
 
-def build_binding() -> str:
+def build_binding() -> str | None:
     """The Python binding's native marshalling: a CPython extension over
     torch's tensor headers.  It calls the C ABI through addresses the binding
-    hands it, so it links against torch only (already loaded when imported)."""
+    hands it, so it links against torch only (already loaded when imported).
+    Without a host compiler or those headers there is none (and none of an
+    earlier build), and the binding goes through ctypes."""
     import sysconfig
 
     import torch
 
     t = os.path.dirname(os.path.abspath(torch.__file__))
+    py = sysconfig.get_paths()["include"]
+    cxx = os.environ.get("CXX", "g++")
+    headers = [os.path.join(t, "include", "torch", "csrc", "autograd", "python_variable.h"),
+               os.path.join(py, "Python.h")]
+    missing = ([] if shutil.which(cxx) else [cxx]) + [h for h in headers if not os.path.exists(h)]
+    if missing:
+        print(f"native binding not built (calls go through ctypes): no {', '.join(missing)}",
+              file=sys.stderr)
+        if os.path.exists(FAST_LIB):
+            os.remove(FAST_LIB)
+        return None
     tmp = FAST_LIB + ".tmp"
-    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared",
+    cmd = [cxx, "-std=c++17", "-O2", "-fPIC", "-shared",
            "-fvisibility=hidden", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           "-isystem", os.path.join(t, "include"), "-I" + sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(t, "include"), "-I" + py,
            os.path.join(PKG, "binding", "fast.cpp"), "-o", tmp,
            "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, capture_output=True, text=True)

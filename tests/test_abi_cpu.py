@@ -371,6 +371,31 @@ def test_python_wrappers_refuse_cpu_tensors(lib):
         spec.score(q_r.float(), K_r, torch.zeros(1, dtype=torch.int32))
 
 
+def test_binding_without_native_marshalling(monkeypatch, tmp_path, capsys):
+    """Where the native marshalling cannot be built or is not there, the library
+    builds and loads all the same and calls go through ctypes."""
+    import sys
+
+    from paper_2512_00722_amd import build as b
+
+    old = tmp_path / "_fast.so"
+    old.write_bytes(b"of an earlier build")
+    monkeypatch.setattr(b, "FAST_LIB", str(old))
+    monkeypatch.setenv("CXX", "no-such-compiler")
+    assert b.build_binding() is None and not old.exists()
+    assert "no-such-compiler" in capsys.readouterr().err
+    monkeypatch.setattr(spec, "_lib", None)
+    monkeypatch.setattr(spec, "_fast", None)
+    monkeypatch.setitem(sys.modules, "paper_2512_00722_amd._fast", None)   # not importable
+    assert spec.load_library().spec_version() and spec._fast is None
+
+    class Plain:
+        is_cuda = True
+
+    monkeypatch.setattr(spec.torch, "Tensor", Plain)
+    assert not spec._plain(Plain())
+
+
 def test_host_sanitizers():
     """Every ABI test above, again in a child process against the host
     sanitizer build (spec_api.cpp under AddressSanitizer and
