@@ -1073,7 +1073,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
 }
 
 // Resident wavefront slots the work is sized for: one per SIMD on 256 CUs.
-constexpr int64_t kWaveSlots = (int64_t)kWaves * 256;
+constexpr int64_t kWaveSlots = (int64_t)kWaves * kCUs;
 
 struct AttnPlan {
   int mode, n_split, split;
@@ -1112,7 +1112,6 @@ int attn_col_groups(const Dims& d) { return d.G > 16 ? d.G / 16 : 1; }
 // 2048: 55.0 against 56.4; 160 groups, k = 1536, 960 units, in a step: 26.1
 // against 26.6), with more than 512 groups, and for short selections of 256
 // groups or more (four chunks per wavefront).
-constexpr int kCUs = 256;  // fixed: the workspace size must not depend on the device
 // wave_splits: splits of a selection with one wavefront per unit (wave_plan).
 bool team_plan(const Dims& d, int64_t groups, int wave_splits, AttnPlan* p) {
   const int gu = d.H_kv * attn_col_groups(d);

@@ -22,6 +22,10 @@ struct Dims {
   bool plain;
 };
 
+// Compute units that launch plans are made for: fixed, as the workspace size
+// must not depend on the device.
+constexpr int kCUs = 256;
+
 // ---- workspace geometry (every region aligned to 256 bytes) -------------
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -37,7 +41,6 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // evenly with 256 keep them (8 x 32768 55.5 -> 55.2).
 constexpr int kScoreTokensPerBlock = 256;
 constexpr int kScoreTokensPerBlockMin = 64;
-constexpr int64_t kScoreCUs = 256;  // fixed: the workspace size must not depend on the device
 // Softmax/head-sum kernel: tokens per workgroup.
 constexpr int kSoftTokensPerBlock = 1024;
 
@@ -45,14 +48,14 @@ inline int score_tokens_per_block(const Dims& d) {
   if (d.plain) {  // 256, halved while there are fewer blocks than CUs
     int tpb = kScoreTokensPerBlock;
     while (tpb > kScoreTokensPerBlockMin &&
-           (int64_t)d.B * ((d.L_max + tpb - 1) / tpb) < kScoreCUs)
+           (int64_t)d.B * ((d.L_max + tpb - 1) / tpb) < kCUs)
       tpb /= 2;
     return tpb;
   }
   const int64_t total = (int64_t)d.B * d.L_max;
-  const int64_t round = kScoreCUs * kScoreTokensPerBlock;
+  const int64_t round = (int64_t)kCUs * kScoreTokensPerBlock;
   const int64_t per_cu = total > 2 * round ? (total + round - 1) / round : 2;
-  const int64_t per_seq = kScoreCUs * per_cu / d.B;  // blocks of a sequence
+  const int64_t per_seq = kCUs * per_cu / d.B;  // blocks of a sequence
   if (per_seq < 1) return kScoreTokensPerBlock;
   const int64_t t = ((d.L_max + per_seq - 1) / per_seq + 15) / 16 * 16;
   return (int)(t < kScoreTokensPerBlockMin ? kScoreTokensPerBlockMin

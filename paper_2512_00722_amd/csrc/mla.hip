@@ -162,8 +162,8 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const uint16_t* p) {
 // permute and meet the query pair (q[n], q[n+1]) -- the input's own 32-bit
 // words, staged in LDS -- in one v_dot2_f32_bf16 (exact products, fp32
 // sum): 64 dot products and 8 permutes per row pair for 8 sequences, where
-// unpacking and fp32 FMAs took twice as many instructions.  Up to TB
-// sequences per pass.
+// unpacking and fp32 FMAs took twice as many instructions.  TB >= B: more
+// than 8 sequences take the split kernel.
 constexpr int kAbsBatch = 8;
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -183,69 +183,65 @@ __global__ __launch_bounds__(64) void mla_absorb_kernel(MlaArgs a) {
 #pragma unroll
     for (int i = 0; i < kAbsBatch; ++i) wr[i] = ldg16_stream(w + (size_t)(bt * kAbsBatch + i) * kDC);
   };
-  for (int b0 = 0; b0 < a.B; b0 += TB) {
-    uint4 wa[kAbsBatch], wb[kAbsBatch];
-    load(wa, 0);
-    __syncthreads();  // the previous pass is done with qs2
-    // this head's no-position queries of sequences b0 .. b0+TB-1: four pairs a load
-    for (int e = lane; e < TB * (kDN / 8); e += 64) {
-      const int t = e / (kDN / 8), n8 = e - t * (kDN / 8);
-      const int b = min(b0 + t, a.B - 1);
-      *reinterpret_cast<uint4*>(&qs2[t][4 * n8]) =
-          ldg16(a.q + (((size_t)layer * a.B + b) * a.H + h) * (kDN + kDR) + 8 * n8);
-    }
-    __syncthreads();
-    float acc[TB][8];
+  uint4 wa[kAbsBatch], wb[kAbsBatch];
+  load(wa, 0);
+  // this head's no-position queries of every sequence: four pairs a load
+  for (int e = lane; e < TB * (kDN / 8); e += 64) {
+    const int t = e / (kDN / 8), n8 = e - t * (kDN / 8);
+    const int b = min(t, a.B - 1);
+    *reinterpret_cast<uint4*>(&qs2[t][4 * n8]) =
+        ldg16(a.q + (((size_t)layer * a.B + b) * a.H + h) * (kDN + kDR) + 8 * n8);
+  }
+  __syncthreads();
+  float acc[TB][8];
 #pragma unroll
-    for (int t = 0; t < TB; ++t)
+  for (int t = 0; t < TB; ++t)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[t][j] = 0.f;
-    auto use = [&](const uint4 (&wr)[kAbsBatch], int bt) {
+    for (int j = 0; j < 8; ++j) acc[t][j] = 0.f;
+  auto use = [&](const uint4 (&wr)[kAbsBatch], int bt) {
 #pragma unroll
-      for (int i = 0; i < kAbsBatch / 2; ++i) {
-        const uint32_t* x = reinterpret_cast<const uint32_t*>(&wr[2 * i]);      // row n
-        const uint32_t* y = reinterpret_cast<const uint32_t*>(&wr[2 * i + 1]);  // row n+1
-        uint32_t wp[8];  // (W[n][c], W[n+1][c]) for this lane's 8 latent dims
+    for (int i = 0; i < kAbsBatch / 2; ++i) {
+      const uint32_t* x = reinterpret_cast<const uint32_t*>(&wr[2 * i]);      // row n
+      const uint32_t* y = reinterpret_cast<const uint32_t*>(&wr[2 * i + 1]);  // row n+1
+      uint32_t wp[8];  // (W[n][c], W[n+1][c]) for this lane's 8 latent dims
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          wp[2 * j] = __builtin_amdgcn_perm(y[j], x[j], 0x05040100u);
-          wp[2 * j + 1] = __builtin_amdgcn_perm(y[j], x[j], 0x07060302u);
-        }
-#pragma unroll
-        for (int t = 0; t < TB; ++t) {
-          const uint32_t qp = qs2[t][bt * (kAbsBatch / 2) + i];
-#pragma unroll
-          for (int c = 0; c < 8; ++c) acc[t][c] = dot2_bf16(wp[c], qp, acc[t][c]);
-        }
+      for (int j = 0; j < 4; ++j) {
+        wp[2 * j] = __builtin_amdgcn_perm(y[j], x[j], 0x05040100u);
+        wp[2 * j + 1] = __builtin_amdgcn_perm(y[j], x[j], 0x07060302u);
       }
-    };
-    // the scheduling barriers keep the order as written: a batch's loads are
-    // issued before the other batch is used, so that they are in flight
-    // during it, and a refill comes after the last use of its buffer
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        const uint32_t qp = qs2[t][bt * (kAbsBatch / 2) + i];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[t][c] = dot2_bf16(wp[c], qp, acc[t][c]);
+      }
+    }
+  };
+  // the scheduling barriers keep the order as written: a batch's loads are
+  // issued before the other batch is used, so that they are in flight
+  // during it, and a refill comes after the last use of its buffer
 #pragma unroll 1
-    for (int bt = 0; bt < kDN / kAbsBatch; bt += 2) {
-      load(wb, bt + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      use(wa, bt);
-      __builtin_amdgcn_sched_barrier(0);
-      if (bt + 2 < kDN / kAbsBatch) load(wa, bt + 2);
-      __builtin_amdgcn_sched_barrier(0);
-      use(wb, bt + 1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  for (int bt = 0; bt < kDN / kAbsBatch; bt += 2) {
+    load(wb, bt + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    use(wa, bt);
+    __builtin_amdgcn_sched_barrier(0);
+    if (bt + 2 < kDN / kAbsBatch) load(wa, bt + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    use(wb, bt + 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-      const int b = b0 + t;
-      if (b >= a.B) break;
-      uint16_t* dst = a.qt + (((size_t)layer * a.B + b) * a.H + h) * kQT;
-      uint4 hi, lo;
-      split8(acc[t], hi, lo);
-      *reinterpret_cast<uint4*>(dst + 8 * lane) = hi;
-      *reinterpret_cast<uint4*>(dst + kDC + 8 * lane) = lo;
-      if (lane < kDR / 8) {  // the rotary part, unchanged
-        const uint16_t* src = a.q + (((size_t)layer * a.B + b) * a.H + h) * (kDN + kDR) + kDN;
-        *reinterpret_cast<uint4*>(dst + 2 * kDC + 8 * lane) = ldg16(src + 8 * lane);
-      }
+  for (int t = 0; t < TB; ++t) {
+    if (t >= a.B) break;
+    uint16_t* dst = a.qt + (((size_t)layer * a.B + t) * a.H + h) * kQT;
+    uint4 hi, lo;
+    split8(acc[t], hi, lo);
+    *reinterpret_cast<uint4*>(dst + 8 * lane) = hi;
+    *reinterpret_cast<uint4*>(dst + kDC + 8 * lane) = lo;
+    if (lane < kDR / 8) {  // the rotary part, unchanged
+      const uint16_t* src = a.q + (((size_t)layer * a.B + t) * a.H + h) * (kDN + kDR) + kDN;
+      *reinterpret_cast<uint4*>(dst + 2 * kDC + 8 * lane) = ldg16(src + 8 * lane);
     }
   }
 }
@@ -817,8 +813,6 @@ MlaPlan mla_plan_of(const MlaDims& d, int want, int min_split) {
   p.n_items = (p.n_units + 7) / 8 * 8 * p.n_hg;
   return p;
 }
-
-constexpr int kCUs = 256;  // fixed: the workspace size must not depend on the device
 
 // As many units as CUs or more, of at least 256 tokens.
 MlaPlan mla_base_plan(const MlaDims& d) {
