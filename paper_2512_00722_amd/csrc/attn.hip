@@ -1107,19 +1107,33 @@ int attn_col_groups(const Dims& d) { return d.G > 16 ? d.G / 16 : 1; }
 //   1 x k=4096 (64 query heads) 15.9 -> 11.4, 8 x k=2048 20.3 -> 19.6,
 //   60 x k=300 27.8 -> 18.4, 50 ragged, k=1200 58.0 -> 53.0;
 //   61 ragged, k=1500, 4 KV heads 47.4 -> 40.9; 24 layers x 2 ragged, k=1000 48.8 -> 42.6.
-// One wavefront per unit stays better where its units just fill the
-// wavefronts (256 groups, k = 4096, 1024 units: 96.3 against 102.5 us; k =
-// 2048: 55.0 against 56.4; 160 groups, k = 1536, 960 units, in a step: 26.1
-// against 26.6), with more than 512 groups, and for short selections of 256
-// groups or more (four chunks per wavefront).
-// wave_splits: splits of a selection with one wavefront per unit (wave_plan).
-bool team_plan(const Dims& d, int64_t groups, int wave_splits, AttnPlan* p) {
+// One wavefront per unit stays better with more than 512 groups, for short
+// selections of 256 groups or more (four chunks per wavefront), where its units
+// just fill the wavefronts with equal or per-head selections (see below), and
+// where it puts several units on every CU while this plan leaves CUs idle, or
+// a selection too long for the splits that would fill them (132 groups, k =
+// 4096, direct: 64.0 against 82.4 us; 144 groups, k = 1000, direct: 22.2
+// against 25.7; 96 groups, k = 2048, 5 splits: 22.6 against 24.1).  That is
+// decided by a second estimate, which counts what a launch takes besides
+// streaming: fitted to 1143 launches of 4 to 512 groups, k = 200 to 6000, it
+// picks the slower plan by more than 5% in 5 of them, where one wavefront per
+// unit without it would be the better choice by up to 33%.
+// Units that just fill the wavefronts (15/16 of them or more): one wavefront
+// per unit -> this plan, 256 groups of k = 4096 94.7 -> 102.9 us, per-head sets
+// of 160 groups, k = 1536, in a step 26.1 -> 26.6; but ragged selections shared by
+// the heads gain by this plan (160 groups, k = 1536 24.5 -> 22.1; 192, k = 1100
+// 23.9 -> 22.7) and equal ones are within 2% (29.6 -> 28.9; 28.7 -> 28.9).
+// wave: the plan with one wavefront per unit (wave_plan).
+bool team_plan(const Dims& d, int64_t groups, const AttnPlan& wave, AttnPlan* p) {
   const int gu = d.H_kv * attn_col_groups(d);
-  const int64_t units = groups * wave_splits;
+  const int64_t units = groups * wave.n_split;
   if (units <= kWaveSlots && units >= kWaveSlots / 16 * 15) return false;
   if (groups >= kCUs && d.k_max <= 4 * kChunk) return false;
   auto cost = [](int64_t wgs, int64_t tokens) { return tokens * (0.017 + 3e-5 * wgs); };
-  double best = 1e30;
+  auto time = [](double base, int64_t wgs, int64_t tokens) {
+    return base + tokens * (0.0125 + 3e-5 * wgs);
+  };
+  double best = 1e30, est = 0;
   // direct: one workgroup per group, or per two where they fill the CUs
   const int dh = groups <= kCUs ? 1 : 2;  // heads per workgroup
   const int64_t dw = groups / dh;
@@ -1127,6 +1141,7 @@ bool team_plan(const Dims& d, int64_t groups, int wave_splits, AttnPlan* p) {
   if (gu % dh == 0 && dw <= kCUs && (dh == 1 || dw >= 3 * kCUs / 4) &&
       W / dh * kTeamRows >= d.k_max) {
     best = cost(dw, (int64_t)d.k_max * dh);
+    est = time(dh == 1 && attn_col_groups(d) == 1 ? 7 : 6, dw, (int64_t)d.k_max * dh);
     *p = {kDirect, 1, 0, W, dh};
   }
   // split: parts of at least a chunk per wavefront
@@ -1140,9 +1155,15 @@ bool team_plan(const Dims& d, int64_t groups, int wave_splits, AttnPlan* p) {
     const double c = 3.5 + cost(groups / sh * ns, tok * sh);
     if (c < best) {
       best = c;
+      est = time(7, groups / sh * ns, tok * sh);
       *p = {kGlobalPartials, (int)ns, kChunk * P, 4, sh};
     }
   }
+  // one wavefront per unit, several of them on every CU
+  const int64_t per_cu = (units + kCUs - 1) / kCUs;
+  if (per_cu >= 2 && wave.n_split > 1 &&
+      time(units <= kWaveSlots ? 8 : 13, (units + per_cu - 1) / per_cu, per_cu * wave.split) < est)
+    return false;
   return best < 1e30;
 }
 
@@ -1165,7 +1186,7 @@ AttnPlan attn_plan(const Dims& d) {
   const int64_t groups = (int64_t)d.n_layers * d.B * d.H_kv * attn_col_groups(d);
   const AttnPlan wave = wave_plan(d, groups);
   AttnPlan team;
-  return !d.plain && team_plan(d, groups, wave.n_split, &team) ? team : wave;
+  return !d.plain && team_plan(d, groups, wave, &team) ? team : wave;
 }
 
 }  // namespace
