@@ -655,7 +655,13 @@ void mla_attn_kernel(MlaArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kOPitch = kDC + 8;  // LDS pitch of the o~ tiles (elements)
 
-// TB: sequences per pass (the product's 16 columns, or half of them).
+// TB: sequences per pass (the product's 16 columns, half or a quarter of them).
+// Rows past the batch repeat its last sequence's loads, which is not free where
+// splits are merged: 1 to 4 sequences in passes of 8 read up to 128 KiB of them
+// per workgroup, as much as the head's weights (8 layers x 128 heads, k = 2048, 1
+// sequence: 39.5 us in passes of 8, 30.8 in passes of 4; 20 layers, k = 1200
+// 87.5 -> 68.0.  Branches around the loads instead: slower, 93 us a call against
+// 91 without them and 83 so).
 // kSplits: selections are split (else the partials are the one split's).
 template <int TB, bool kSplits>
 __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
@@ -689,7 +695,7 @@ __global__ __launch_bounds__(kMThreads, 2) void mla_out_kernel(MlaArgs a) {
     for (int s = 0; s < kDC / 32; ++s) wr[s] = ldg16(wp + 32 * s);
   }
   constexpr int kItems = TB * (kDC / 8) / kMThreads;  // (sequence, 8 dims) items per thread
-  constexpr int kBatch = kSplits ? 8 / kItems : 1;    // splits requested together
+  constexpr int kBatch = kSplits ? (kItems == 4 ? 2 : 4) : 1;  // splits requested together
   for (int b0 = 0; b0 < a.B; b0 += TB) {
     // Everything the merge reads first is requested before the first wait: the
     // first splits' partials of this thread's items and one (sequence, split)
@@ -936,7 +942,10 @@ hipError_t launch_mla(const MlaDims& d, const uint16_t* q, const uint16_t* ckv,
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 go(2 * grid_lh), to(kMThreads);
-  if (d.B <= 8) {
+  if (d.B <= 4) {
+    if (p.n_split > 1) hipLaunchKernelGGL((mla_out_kernel<4, true>), go, to, 0, s, a);
+    else hipLaunchKernelGGL((mla_out_kernel<4, false>), go, to, 0, s, a);
+  } else if (d.B <= 8) {
     if (p.n_split > 1) hipLaunchKernelGGL((mla_out_kernel<8, true>), go, to, 0, s, a);
     else hipLaunchKernelGGL((mla_out_kernel<8, false>), go, to, 0, s, a);
   } else {

@@ -91,8 +91,8 @@ def test_mla_cases(dev, case):
 
 # (B, L, k_max, n_layers, H, counts): both forms of the absorb kernel (one
 # wavefront a head above 1024 heads and up to 8 sequences; half heads
-# otherwise, in passes of 1, 4 or 8 sequences) and both of the output kernel
-# (8 and 16 sequences a pass), with a remainder in each, and split counts that
+# otherwise, in passes of 1, 4 or 8 sequences) and all of the output kernel
+# (4, 8 and 16 sequences a pass), with a remainder in each, and split counts that
 # are no multiple of the splits it requests together
 FORM_CASES = [
     (1, 80, 30, 17, 64, [30]),
