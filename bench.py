@@ -91,18 +91,32 @@ def attn_source_digest(sources=ATTN_SOURCES):
     return h.hexdigest()
 
 
-def stored_traffic(workload, path=TRAFFIC_FILE, sources=ATTN_SOURCES):
-    """Per-launch HBM bytes of a kernel (default: the attention) on
-    `workload`, measured with rocprofv3 PMC counters; valid only for the code
-    they were taken on."""
+def stored_counters(workload, path, sources):
+    """What a profiled run recorded of a launch on `workload` (its kernels and
+    HBM bytes, from rocprofv3); valid only for the code it was taken on, else
+    empty."""
     try:
         with open(path) as f:
             t = json.load(f)
         if t.get("attn_code_sha256", t.get("code_sha256")) != attn_source_digest(sources):
-            return None
-        return t.get("workloads", {}).get(workload, {}).get("bytes_per_launch")
+            return {}
+        return t.get("workloads", {}).get(workload, {})
     except (OSError, ValueError):
-        return None
+        return {}
+
+
+def stored_traffic(workload, path=TRAFFIC_FILE, sources=ATTN_SOURCES):
+    """Per-launch HBM bytes of a kernel (default: the attention) on
+    `workload`, measured with rocprofv3 PMC counters."""
+    return stored_counters(workload, path, sources).get("bytes_per_launch")
+
+
+def attn_kernels(workload, head_level=False):
+    """The kernels of an attention launch on `workload`, as profiled (which of
+    them run depends on the launch plan); the source file where that is not
+    known: other code, or one token set per KV head."""
+    k = {} if head_level else stored_counters(workload, TRAFFIC_FILE, ATTN_SOURCES)
+    return " + ".join(k.get("kernels") or ["csrc/attn.hip"])
 
 
 def cpu_model():
@@ -380,11 +394,7 @@ def run_fixed(args, spec, w, x, name):
             "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4),
             "traffic": traffic,
-            # the partials workspace exists only when selections are split (then a
-            # second kernel merges them)
-            "kernel": "sparse GQA decode attention (attn_split_kernel"
-                      + (" + attn_combine_kernel)" if spec.workspace_size(dims_a, spec.OP_ATTN) > 0
-                         else ")"),
+            "kernel": f"sparse GQA decode attention ({attn_kernels(name, args.head_level)})",
             "bytes_per_launch": a_bytes,
             "avg_launch_us": round(op_us["attn"], 2),
         },
@@ -588,9 +598,9 @@ def run_elastic(args, spec, w, x, e, algorithmic_bytes):
             "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4),
             "traffic": stored_traffic(w.name),
-            "kernel": ("sparse GQA decode attention over the slot buffers (attn_split_kernel)"
-                       if copy_path else "sparse GQA decode attention over the slots, loading "
-                       "the update's rows (attn_split_kernel)"),
+            "kernel": ("sparse GQA decode attention over the slot"
+                       + (" buffers" if copy_path else "s, loading the update's rows")
+                       + f" ({attn_kernels(w.name)})"),
             "bytes_per_launch": a_bytes,
             "avg_launch_us": round(attn_us, 2),
         },

@@ -104,3 +104,26 @@ def test_frontend_scale_and_bytes():
     assert WORKLOADS["b1_l4096_k512_1layer"].yarn_scale == 2.0
     # two 512 x 4096 bf16 matrices, 8 embedding rows, q_r and the new K_r row
     assert frontend_bytes(w) == 2 * 512 * 4096 * 2 + 8 * 4096 * 2 + 2 * 8 * 512 * 2
+
+
+def test_benchmark_names_the_profiled_kernels(monkeypatch, tmp_path):
+    """The roofline's kernels and traffic are those of a profiled run of this
+    code; other code, per-head sets and unprofiled workloads name none."""
+    import json
+
+    import bench
+
+    f = tmp_path / "traffic.json"
+    monkeypatch.setattr(bench, "TRAFFIC_FILE", str(f))
+
+    def store(digest):
+        f.write_text(json.dumps({"attn_code_sha256": digest, "workloads": {
+            "w": {"kernels": ["attn_team_kernel", "attn_combine_kernel"]}}}))
+
+    assert bench.attn_kernels("w") == "csrc/attn.hip"       # no file
+    store(bench.attn_source_digest())
+    assert bench.attn_kernels("w") == "attn_team_kernel + attn_combine_kernel"
+    assert bench.attn_kernels("w", head_level=True) == "csrc/attn.hip"
+    assert bench.attn_kernels("other") == "csrc/attn.hip"
+    store("other code")
+    assert bench.attn_kernels("w") == "csrc/attn.hip"
