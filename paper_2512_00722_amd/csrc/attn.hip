@@ -1101,33 +1101,40 @@ int attn_col_groups(const Dims& d) { return d.G > 16 ? d.G / 16 : 1; }
 // streams its tokens at ~0.017 us each when few CUs stream, ~0.025 us when all
 // do.  Two heads per workgroup read neighbouring pieces of the same rows
 // (2-4% faster on splits of at least 64 groups; 128 groups, k = 2048: 32.2 ->
-// 30.0 us); fewer, larger partials are better below that.  us per launch, one
-// wavefront per unit -> this plan, one layer, 32 query heads, 8 KV heads:
-//   1 x k=128 8.8 -> 5.5, 1 x k=512 9.2 -> 8.3, 9 x k=321 15.1 -> 10.4,
-//   1 x k=4096 (64 query heads) 15.9 -> 11.4, 8 x k=2048 20.3 -> 19.6,
-//   60 x k=300 27.8 -> 18.4, 50 ragged, k=1200 58.0 -> 53.0;
-//   61 ragged, k=1500, 4 KV heads 47.4 -> 40.9; 24 layers x 2 ragged, k=1000 48.8 -> 42.6.
-// One wavefront per unit stays better with more than 512 groups, for short
-// selections of 256 groups or more (four chunks per wavefront), where its units
-// just fill the wavefronts with equal or per-head selections (see below), and
-// where it puts several units on every CU while this plan leaves CUs idle, or
-// a selection too long for the splits that would fill them (132 groups, k =
-// 4096, direct: 64.0 against 82.4 us; 144 groups, k = 1000, direct: 22.2
-// against 25.7; 96 groups, k = 2048, 5 splits: 22.6 against 24.1).  That is
-// decided by a second estimate, which counts what a launch takes besides
-// streaming: fitted to 1143 launches of 4 to 512 groups, k = 200 to 6000, it
-// picks the slower plan by more than 5% in 5 of them, where one wavefront per
-// unit without it would be the better choice by up to 33%.
-// Units that just fill the wavefronts (15/16 of them or more): one wavefront
-// per unit -> this plan, 256 groups of k = 4096 94.7 -> 102.9 us, per-head sets
-// of 160 groups, k = 1536, in a step 26.1 -> 26.6; but ragged selections shared by
-// the heads gain by this plan (160 groups, k = 1536 24.5 -> 22.1; 192, k = 1100
-// 23.9 -> 22.7) and equal ones are within 2% (29.6 -> 28.9; 28.7 -> 28.9).
+// 30.0 us); fewer, larger partials are better below that.  us per launch in a
+// HIP graph, one wavefront per unit -> this plan, one layer, 32 query heads, 8
+// KV heads:
+//   1 x k=128 8.8 -> 5.7, 1 x k=512 9.3 -> 8.4, 9 x k=321 14.6 -> 8.4,
+//   1 x k=4096 (64 query heads) 15.7 -> 10.0, 8 x k=2048 17.9 -> 17.5,
+//   60 x k=300 27.2 -> 18.3, 50 ragged, k=1200 50.8 -> 43.6;
+//   61 ragged, k=1500, 4 KV heads 42.1 -> 34.2; 24 layers x 2 ragged, k=1000 44.1 -> 32.6.
+//
+// One wavefront per unit stays better
+//  - with more than 512 groups, and for short selections of 256 groups or more
+//    (four chunks per wavefront);
+//  - where its units, of full length, just fill the wavefronts and the
+//    selections are equal or per head: 256 groups, k = 4096 94.7 against 102.9
+//    us, per-head sets of 160 groups, k = 1536, in a step 26.1 against 26.6.
+//    (Ragged selections shared by the heads would gain: 160 groups, k = 1536
+//    24.5 -> 22.1; equal ones are within 2%.  Units of which many are short do
+//    not fill them: 480 to 512 groups, k = 260 to 400, are the 24 to 29 us that
+//    this plan does in 15 to 23.);
+//  - where it puts several units on every CU while this plan leaves CUs idle,
+//    or has a selection too long for the splits that would fill them: 136
+//    groups, k = 4096, direct 63.2 against 84.2 us; 144 groups, k = 1000, direct
+//    22.2 against 25.7; 96 groups, k = 2048, 5 splits 22.6 against 24.1.  That
+//    is decided by a second estimate, which counts what a launch takes besides
+//    streaming.  Of 1800 one-layer launches (1 to 124 sequences, 2 to 8 KV heads,
+//    k = 100 to 6000, equal and ragged, rows not in the caches) it leaves 32
+//    more than 3% slower than with one wavefront per unit throughout (at most
+//    10%: 48 to 56 groups, k = 1750 to 2048), against 142 (up to 31%) without.
 // wave: the plan with one wavefront per unit (wave_plan).
 bool team_plan(const Dims& d, int64_t groups, const AttnPlan& wave, AttnPlan* p) {
   const int gu = d.H_kv * attn_col_groups(d);
   const int64_t units = groups * wave.n_split;
-  if (units <= kWaveSlots && units >= kWaveSlots / 16 * 15) return false;
+  if (units <= kWaveSlots && units >= kWaveSlots / 16 * 15 &&
+      10 * (int64_t)d.k_max >= 9 * (int64_t)wave.n_split * wave.split)
+    return false;
   if (groups >= kCUs && d.k_max <= 4 * kChunk) return false;
   auto cost = [](int64_t wgs, int64_t tokens) { return tokens * (0.017 + 3e-5 * wgs); };
   auto time = [](double base, int64_t wgs, int64_t tokens) {
