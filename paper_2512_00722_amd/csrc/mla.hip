@@ -256,10 +256,11 @@ __global__ __launch_bounds__(64) void mla_absorb_kernel(MlaArgs a) {
 // then over the wavefronts in LDS.
 //
 // us per call, one wavefront a head -> this: 1 layer x 128 heads, 8 sequences
-// (the kernel alone) 16.9 -> 7.9; 32 sequences, all three kernels 107 -> 62; 8
-// layers x 128 heads, 8 sequences, 141 -> 140; 16 layers 250 -> 255: there the
-// chip is full either way and the LDS sums cost more than they save, unless
-// more than 8 sequences would read W_UK again.
+// (the kernel alone) 16.9 -> 7.9; 3 layers, 2 sequences of k = 64, the call 40.8
+// -> 39.4, 8 of them 48.1 -> 44.3; 8 layers 64.8 -> 66.2 and 74.6 -> 74.3; above
+// that the chip is full either way and the LDS sums cost more than they save,
+// unless more than 8 sequences would read W_UK again (1 layer, 32 x k = 2048, the
+// call with both kernels' changes 124 -> 77).
 constexpr int kAbsDims = kDC / 2;  // latent dims of a workgroup
 constexpr int kAbsSplitHeads = 1024;  // (layer, head) pairs up to which it is taken
 
@@ -845,7 +846,10 @@ MlaPlan mla_base_plan(const MlaDims& d) {
 // k=300 120 -> 98), but not above that (13 layers, 5 ragged x k=2048 162 -> 177)
 // or where it has none (13 layers, 1 x k=2048 121 -> 127).  Other splits in two
 // rounds are not taken (13 layers, 5 ragged x k=2048, 3 splits instead of the
-// base plan's 2: 188 against 162).
+// base plan's 2: 188 against 162).  The last two limits come from these few
+// shapes; over 2860 launches (1 to 61 layers, 1 to 48 sequences, k = 100 to 2048,
+// weights not in the caches) the choice is more than 3% behind the base plan's
+// in 6.
 MlaPlan mla_plan(const MlaDims& d) {
   const MlaPlan base = mla_base_plan(d);
   if (d.plain || d.n_layers * d.B * (d.H / 64) >= kCUs) return base;
