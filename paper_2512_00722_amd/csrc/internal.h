@@ -38,10 +38,13 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // pieces per logits row, see score_row_stride): 16 x 4096 25.4 -> 22.8, 1 x
 // 65536 26.0 -> 24.0, 30 ragged x 3000 27.9 -> 23.9, 5 ragged x 20011 (16 heads)
 // 44.3 -> 39.0, 2 x 50000 (16 heads) 53.0 -> 49.6; rows that fill the CUs
-// evenly with 256 keep them (8 x 32768 55.5 -> 55.2).  Of 2040 launches (1 to
-// 260 sequences of 300 to 131072, keys not in the caches) 9 are more than 5%
-// slower than with 256, ragged batches whose blocks fall otherwise over the CUs
-// (30 x 12001 56.7 -> 63.6, 24 x 14000 52.1 -> 59.0); the geometric mean is 0.94.
+// evenly with 256 keep them (8 x 32768 55.5 -> 55.2).  So do rows of six
+// workgroups per CU, of which four are resident: smaller blocks gain 1% there on
+// equal lengths, and on ragged ones nothing on average, while batches that then
+// just miss a single round lose up to 16% (30 x 12001 56.7 -> 63.6, 24 x 14000
+// 52.1 -> 59.0).  Of 2040 launches (1 to 260 sequences of 300 to 131072, keys not
+// in the caches) 2 are more than 5% slower than with blocks of 256; the geometric
+// mean is 0.94.
 constexpr int kScoreTokensPerBlock = 256;
 constexpr int kScoreTokensPerBlockMin = 64;
 // Softmax/head-sum kernel: tokens per workgroup.
@@ -59,7 +62,7 @@ inline int score_tokens_per_block(const Dims& d) {
   const int64_t round = (int64_t)kCUs * kScoreTokensPerBlock;
   const int64_t per_cu = total > 2 * round ? (total + round - 1) / round : 2;
   const int64_t per_seq = kCUs * per_cu / d.B;  // blocks of a sequence
-  if (per_seq < 1) return kScoreTokensPerBlock;
+  if (per_seq < 1 || per_cu == 6) return kScoreTokensPerBlock;
   const int64_t t = ((d.L_max + per_seq - 1) / per_seq + 15) / 16 * 16;
   return (int)(t < kScoreTokensPerBlockMin ? kScoreTokensPerBlockMin
                : t > kScoreTokensPerBlock  ? kScoreTokensPerBlock
