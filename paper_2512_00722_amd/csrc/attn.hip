@@ -1101,7 +1101,10 @@ int attn_col_groups(const Dims& d) { return d.G > 16 ? d.G / 16 : 1; }
 // streams its tokens at ~0.017 us each when few CUs stream, ~0.025 us when all
 // do.  Two heads per workgroup read neighbouring pieces of the same rows
 // (2-4% faster on splits of at least 64 groups; 128 groups, k = 2048: 32.2 ->
-// 30.0 us); fewer, larger partials are better below that.  us per launch in a
+// 30.0 us); fewer, larger partials are better below that, unless the two read
+// the same rows (more than 16 query heads per KV head) and there are 300 tokens
+// per CU: 60 groups, k = 1750 20.5 -> 19.1, 28 groups, k = 6000 25.0 -> 23.1,
+// but 24 groups, k = 1000 12.1 -> 12.5.  us per launch in a
 // HIP graph, one wavefront per unit -> this plan, one layer, 32 query heads, 8
 // KV heads:
 //   1 x k=128 8.8 -> 5.7, 1 x k=512 9.3 -> 8.4, 9 x k=321 14.6 -> 8.4,
@@ -1152,7 +1155,8 @@ bool team_plan(const Dims& d, int64_t groups, const AttnPlan& wave, AttnPlan* p)
     *p = {kDirect, 1, 0, W, dh};
   }
   // split: parts of at least a chunk per wavefront
-  const int sh = gu % 2 == 0 && groups >= 64 ? 2 : 1;
+  const bool same_rows = attn_col_groups(d) > 1 && groups * d.k_max >= 300 * kCUs;
+  const int sh = gu % 2 == 0 && (groups >= 64 || same_rows) ? 2 : 1;
   const int P = 4 / sh;
   const int64_t chunks = (d.k_max + kChunk - 1) / kChunk;
   int64_t ns = kCUs * sh / groups;

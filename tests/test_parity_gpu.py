@@ -308,6 +308,9 @@ TEAM_CASES = [
     (1, 12, 1300, 16, 8, [(103 * b) % 1201 for b in range(12)], 1200),
     # column groups of more than 16 query heads
     (1, 3, 900, 64, 2, [600, 31, 577], 600),
+    # split, the two column groups of a KV head in one workgroup (24 and 48 groups)
+    (1, 6, 3300, 64, 2, [3200, 0, 1, 3199, 1601, 65], 3200),
+    (1, 12, 1700, 64, 2, [(229 * b) % 1601 for b in range(12)], 1600),
 ]
 
 
@@ -725,13 +728,14 @@ ELASTIC_FORMS = [
     # workgroups that share a unit: one group each with four and eight
     # wavefronts (18 and 200 groups), two groups each (400 groups), split with
     # two groups each (64 groups), and the two column groups of a KV head, one of
-    # which writes, in one workgroup (96 groups)
+    # which writes, in one workgroup (96 and 48 groups)
     (1, 9, 400, 8, 2, [0, 1, 31, 32, 33, 127, 128, 129, 200], 200),
     (1, 100, 600, 4, 2, [(61 * b) % 521 for b in range(100)], 520),
     (2, 50, 400, 8, 4, [(37 * b) % 201 for b in range(50)], 200),
     (2, 50, 400, 8, 4, [(37 * b) % 301 for b in range(50)], 300),
     (2, 4, 2100, 16, 8, [2048, 0, 1025, 63], 2048),
     (1, 24, 700, 64, 2, [(103 * b) % 601 for b in range(24)], 600),
+    (1, 12, 1700, 64, 2, [(229 * b) % 1601 for b in range(12)], 1600),
     # one wavefront per unit: pipelined (1280 units), and split cold (960)
     (5, 32, 160, 16, 8, [(37 * b) % 129 for b in range(32)], 128),
     (4, 5, 1600, 8, 8, [1536, 1001, 0, 33, 257], 1536),
