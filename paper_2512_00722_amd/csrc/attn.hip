@@ -1128,9 +1128,10 @@ int attn_col_groups(const Dims& d) { return d.G > 16 ? d.G / 16 : 1; }
 //    22.2 against 25.7; 96 groups, k = 2048, 5 splits 22.6 against 24.1.  That
 //    is decided by a second estimate, which counts what a launch takes besides
 //    streaming.  Of 1800 one-layer launches (1 to 124 sequences, 2 to 8 KV heads,
-//    k = 100 to 6000, equal and ragged, rows not in the caches) it leaves 32
+//    k = 100 to 6000, equal and ragged, rows not in the caches) it leaves 29
 //    more than 3% slower than with one wavefront per unit throughout (at most
-//    10%: 48 to 56 groups, k = 1750 to 2048), against 142 (up to 31%) without.
+//    7%: 48 to 56 groups, k = 2048, and 8 to 24 groups, k = 300 of equal length,
+//    whose ragged ones gain as much), against 142 (up to 31%) without.
 // wave: the plan with one wavefront per unit (wave_plan).
 bool team_plan(const Dims& d, int64_t groups, const AttnPlan& wave, AttnPlan* p) {
   const int gu = d.H_kv * attn_col_groups(d);
